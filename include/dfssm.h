@@ -76,21 +76,22 @@ typedef enum { DFSSM_F16 = 0, DFSSM_F32 = 1 } dfssm_dtype;
 
 /* Kernel family selection for dfssm_scaffold_lora_linear_ex. */
 typedef enum {
-  DFSSM_PATH_AUTO = 0,     /* few-token MFMA for M <= 32; for 33..512 the
-                              few-token kernel in 64-token blocks or the
-                              prefill kernel, by a cost model of the two
-                              (see the implementation); prefill MFMA
-                              above 512 */
+  DFSSM_PATH_AUTO = 0,     /* the few-token kernel at 1 and 2 tokens (up to
+                              16 where few rows make it the fastest), else
+                              the split-K tile kernel or the many-token
+                              path, by modelled cost (see the
+                              implementation) */
   DFSSM_PATH_DECODE = 1,   /* bit-plane popcount GEMV (any M, best for M <= 4) */
-  DFSSM_PATH_MFMA = 2,     /* sign bits expanded on chip + int8 MFMA, tiles of
-                              128 tokens (prefill): an 8-wave ping-pong
-                              kernel where each block gets at least 24 row
-                              tiles of 16, a 4-wave kernel otherwise
-                              (dfssm_test_switch can force one of them). */
+  DFSSM_PATH_MFMA = 2,     /* sign bits expanded on chip + int8 MFMA: the
+                              split-K tile kernel, or for many tokens
+                              (prefill) a down-projection launch and tiles
+                              of 128 tokens x 128 or 256 rows
+                              (dfssm_test_switch can force one of these). */
   DFSSM_PATH_MFMA_FEW = 3  /* the same expansion and MFMA for M <= 512 in
-                              one launch: 16 output rows and up to 32
-                              tokens per workgroup (64 above 32 tokens), K
-                              split over its waves, the LoRA
+                              one launch: 16 output rows and up to 16
+                              tokens per workgroup (few-token kernel), or
+                              tiles of 16 to 64 of each (split-K tile
+                              kernel), K split over the waves, the LoRA
                               down-projection in workgroups of the same
                               grid; M > 512 gives DFSSM_ERR_UNSUPPORTED. */
 } dfssm_path;
@@ -174,9 +175,9 @@ dfssm_status dfssm_scaffold_lora_linear_ex(const int8_t* q, const float* s, int6
  *   B4 [N][r/2] bytes (row n holds B[n, 0..r-1])
  * r must be even.  Every other argument, output and result is as in
  * dfssm_scaffold_lora_linear_ex on the unpacked A and B (the same exact
- * integers).  The few-token path (M <= 32) reads the packed bytes directly,
- * half the LoRA bytes of int8; the prefill MFMA and popcount paths first
- * expand the factors to int8 inside the workspace.  The workspace must hold
+ * integers).  The MFMA kernels read the packed bytes directly, half the LoRA
+ * bytes of int8; the popcount path first expands the factors to int8 inside
+ * the workspace.  The workspace must hold
  * dfssm_linear_i4_workspace_bytes(M, K, N, r) bytes.
  * Errors: NULL, SHAPE, ALIGN, WORKSPACE, UNSUPPORTED, DEVICE. */
 size_t dfssm_linear_i4_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t r);
@@ -556,12 +557,13 @@ dfssm_status dfssm_mamba2_status(const dfssm_mamba2_model* model, int64_t M, con
  * which leaves every choice automatic; a test sets a switch, runs its
  * calls, and sets it back to 0).  Results are the same integers and bits
  * on every choice; only the kernels that compute them change.
- *   DFSSM_TEST_LOCAL_LORA          1: the few-token kernel launches no LoRA
- *                                  workgroups; every output workgroup
+ *   DFSSM_TEST_LOCAL_LORA          1: the few-token and split-K tile kernels
+ *                                  launch no LoRA workgroups; every output workgroup
  *                                  computes acc_a itself (the path it takes
  *                                  when the exchange words never arrive)
- *   DFSSM_TEST_PREFILL_KERNEL      4 or 8: the 4-wave or the 8-wave prefill
- *                                  kernel on the prefill path
+ *   DFSSM_TEST_PREFILL_KERNEL      4 or 8: the 128-row or the 256-row tiles
+ *                                  of the many-token path on
+ *                                  DFSSM_PATH_MFMA
  *   DFSSM_TEST_LM_HEAD_MFMA_TOKENS n > 0: the LM head runs on the matrix
  *                                  cores from n tokens instead of 8
  *   DFSSM_TEST_LM_HEAD_TILED_TOKENS n > 0: on the matrix cores, the tiled

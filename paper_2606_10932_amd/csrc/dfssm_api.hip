@@ -69,72 +69,71 @@ size_t linear_ws_bytes(int64_t M, int64_t K, int64_t r) {
   return dfssm::carve_linear_workspace(nullptr, M, K, r).bytes;
 }
 
-// Kernel family of the automatic path: the popcount GEMV up to kDecodeM0
-// tokens (none by default); the one-launch few-token MFMA kernel up to
-// kSkinnyMaxTokens; above, whichever of the few-token kernel in 64-token
-// blocks and the prefill path a cost model puts lower (us), fitted on
-// MI355X to the 130M, 1.3B and 2.7B projections at 33 to 512 tokens:
-//   few-token  9.5 + 0.013 B (0.76 + K/2048) + 1.5 ceil(M/64) K/2048,
-//              B = ceil(M/16) ceil(N/16) / 4
-//   prefill    dfssm::prefill_cost_us (its K-loop stages, its slices and
-//              the form its tiling takes)
-// The few-token kernel's cost grows with its 16-token tiles (a partly
-// filled 64-token block costs its tiles) and its 64-token blocks.  On the
-// 72 measured cases the chosen kernel is within 0.9 us (and 5%) of the
-// faster one.
-int auto_path(int64_t M, int64_t K, int64_t N) {
-  if (M <= dfssm::kDecodeM0) return DFSSM_PATH_DECODE;
-  if (M <= dfssm::kSkinnyMaxTokens) return DFSSM_PATH_MFMA_FEW;
-  if (M > dfssm::kSkinnyChunkedMaxTokens) return DFSSM_PATH_MFMA;
-  const double k2 = (double)K / 2048.0;
-  const double B = (double)dfssm::ceil_div(M, 16) * (double)dfssm::ceil_div(N, 16) / 4.0;
-  const double few = 9.5 + 0.013 * B * (0.76 + k2) + 1.5 * (double)dfssm::ceil_div(M, 64) * k2;
-  return few <= dfssm::prefill_cost_us(M, K, N) ? DFSSM_PATH_MFMA_FEW : DFSSM_PATH_MFMA;
+// The kernels of a linear.
+enum Kernel { kPopcount, kFew, kMid, kTile };
+
+// The few-token kernel where it is the fastest one (measured against the
+// split-K tile kernel at 1 to 17 tokens on eight projections, us per call): at
+// 1 and 2 tokens, where its LoRA words reach the output workgroups sooner (1.3B
+// in_proj 5.8 / 6.2 against 6.3 / 6.5, out_proj 5.7 / 5.8 against 6.4 / 6.3),
+// unless its 16-row workgroups outnumber two per CU (2.7B in_proj 7.6 against
+// 6.6) or the rank is small and the rows many (130M in_proj, r = 16: 6.6
+// against 5.7); and up to 16 tokens for few rows of at least 2048 columns (its
+// 16-byte sign loads; 2048 -> 1024: 5.3-5.7 against 5.9).
+bool few_is_best(int64_t M, int64_t K, int64_t N, int64_t r) {
+  if (M > dfssm::kSkinnyMaxTokens) return false;
+  if (N <= 1024 && K >= 2048) return true;
+  return M <= 2 && (N <= 2048 || (r > 32 && N <= 8704));
 }
 
-// Kernel family for a linear (path already chosen or AUTO).
+// Kernel of a linear on a path.  AUTO takes the few-token kernel where it is
+// best, else the cheaper of the split-K tile kernel (its words permitting) and
+// the many-token path by their modelled costs; MFMA_FEW the first two, MFMA the
+// last two.
+Kernel choose(int path, int64_t M, int64_t K, int64_t N, int64_t r) {
+  if (path == DFSSM_PATH_DECODE) return kPopcount;
+  if (path != DFSSM_PATH_MFMA && few_is_best(M, K, N, r)) return kFew;
+  if (path == DFSSM_PATH_MFMA_FEW) return kMid;
+  if (path == DFSSM_PATH_MFMA && dfssm::test_switch(DFSSM_TEST_PREFILL_KERNEL) != 0) return kTile;
+  return dfssm::mid_takes(M, r) && dfssm::mid_cost_us(M, K, N, r) <= dfssm::tile_cost_us(M, K, N) ? kMid : kTile;
+}
+
+// The linear after validation, with int8 factors or (l4) packed int4 ones,
+// which only the popcount kernels cannot read: for them `extra` is room for
+// the expanded factors (dfssm::linear_i4_workspace_bytes).
 hipError_t launch_linear(int path, const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N, int64_t r,
-                         const uint32_t* w_bits, const float* alpha, const int8_t* A, const int8_t* B,
+                         const uint32_t* w_bits, const float* alpha, const void* A, const void* B, bool l4,
                          const float* beta, float* y, int32_t* acc_s, int32_t* acc_a, int64_t* acc_b,
-                         const dfssm::LinearWorkspace& ws, hipStream_t hs) {
-  if (path == DFSSM_PATH_AUTO) path = auto_path(M, K, N);
-  if (path == DFSSM_PATH_DECODE)
-    return dfssm::launch_decode_linear(q, s, M, K, N, r, w_bits, alpha, A, B, beta, y, acc_s, acc_a, acc_b, ws,
+                         const dfssm::LinearWorkspace& ws, void* extra, hipStream_t hs) {
+  const int8_t *A8 = static_cast<const int8_t*>(A), *B8 = static_cast<const int8_t*>(B);
+  const uint8_t *A4 = static_cast<const uint8_t*>(A), *B4 = static_cast<const uint8_t*>(B);
+  l4 = l4 && r > 0;
+  switch (choose(path, M, K, N, r)) {
+    case kFew:
+      return l4 ? dfssm::launch_skinny_linear_i4(q, s, M, K, N, r, w_bits, alpha, A4, B4, beta, y, acc_s, acc_a, acc_b,
+                                                 ws, hs)
+                : dfssm::launch_skinny_linear(q, s, M, K, N, r, w_bits, alpha, A8, B8, beta, y, acc_s, acc_a, acc_b,
+                                              ws, hs);
+    case kMid:
+      return l4 ? dfssm::launch_mid_linear_i4(q, s, M, K, N, r, w_bits, alpha, A4, B4, beta, y, acc_s, acc_a, acc_b,
+                                              ws, hs)
+                : dfssm::launch_mid_linear(q, s, M, K, N, r, w_bits, alpha, A8, B8, beta, y, acc_s, acc_a, acc_b, ws,
+                                           hs);
+    case kTile:
+      return dfssm::launch_tile_linear(q, s, M, K, N, r, w_bits, alpha, A8, B8, l4, beta, y, acc_s, acc_a, acc_b, ws,
                                        hs);
-  if (path == DFSSM_PATH_MFMA_FEW)
-    return dfssm::launch_skinny_linear(q, s, M, K, N, r, w_bits, alpha, A, B, beta, y, acc_s, acc_a, acc_b, ws,
-                                       hs);
-  return dfssm::launch_mfma_linear(q, s, M, K, N, r, w_bits, alpha, A, B, beta, y, acc_s, acc_a, acc_b, ws, hs);
-}
-
-// The int4 linear after validation: the few-token kernel reads the packed
-// factors itself; the other paths run the int8 kernels on factors expanded
-// into the workspace (linear_i4_workspace_bytes of it).
-hipError_t launch_linear_i4(int path, const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N, int64_t r,
-                            const uint32_t* w_bits, const float* alpha, const uint8_t* A4, const uint8_t* B4,
-                            const float* beta, float* y, int32_t* acc_s, int32_t* acc_a, int64_t* acc_b,
-                            void* workspace, hipStream_t hs) {
-  dfssm::LinearWorkspace ws = dfssm::carve_linear_workspace(workspace, M, K, r);
-  if (path == DFSSM_PATH_AUTO) path = auto_path(M, K, N);
-  hipError_t e;
-  if (path == DFSSM_PATH_MFMA_FEW || r == 0) {
-    if (path == DFSSM_PATH_MFMA_FEW)
-      e = dfssm::launch_skinny_linear_i4(q, s, M, K, N, r, w_bits, alpha, A4, B4, beta, y, acc_s, acc_a, acc_b, ws,
-                                         hs);
-    else
-      e = launch_linear(path, q, s, M, K, N, 0, w_bits, alpha, nullptr, nullptr, nullptr, y, acc_s, acc_a, acc_b,
-                        ws, hs);
-  } else {
-    // the int8 kernels on factors expanded into the workspace
-    char* extra = static_cast<char*>(workspace) + dfssm::linear_i4_extra_offset(M, K, r);
-    int8_t* A8 = reinterpret_cast<int8_t*>(extra);
-    int8_t* B8 = reinterpret_cast<int8_t*>(extra + (((size_t)(r * K) + 255) & ~(size_t)255));
-    e = dfssm::launch_unpack_int4(A4, r * K, A8, hs);
-    if (e == hipSuccess) e = dfssm::launch_unpack_int4(B4, N * r, B8, hs);
-    if (e == hipSuccess)
-      e = launch_linear(path, q, s, M, K, N, r, w_bits, alpha, A8, B8, beta, y, acc_s, acc_a, acc_b, ws, hs);
+    default: break;
   }
-  return e;
+  if (l4) {
+    int8_t* ax = static_cast<int8_t*>(extra);
+    int8_t* bx = ax + (((size_t)(r * K) + 255) & ~(size_t)255);
+    hipError_t e = dfssm::launch_unpack_int4(A4, r * K, ax, hs);
+    if (e == hipSuccess) e = dfssm::launch_unpack_int4(B4, N * r, bx, hs);
+    if (e != hipSuccess) return e;
+    A8 = ax;
+    B8 = bx;
+  }
+  return dfssm::launch_decode_linear(q, s, M, K, N, r, w_bits, alpha, A8, B8, beta, y, acc_s, acc_a, acc_b, ws, hs);
 }
 
 }  // namespace
@@ -215,9 +214,9 @@ dfssm_status dfssm_scaffold_lora_linear_ex(const int8_t* q, const float* s, int6
   if (path != DFSSM_PATH_AUTO && path != DFSSM_PATH_DECODE && path != DFSSM_PATH_MFMA &&
       path != DFSSM_PATH_MFMA_FEW)
     return fail(DFSSM_ERR_SHAPE, "path=%d", path);
-  if (path == DFSSM_PATH_MFMA_FEW && M > dfssm::kSkinnyChunkedMaxTokens)
+  if (path == DFSSM_PATH_MFMA_FEW && M > dfssm::kFewPathMaxTokens)
     return fail(DFSSM_ERR_UNSUPPORTED, "path=%d takes M <= %lld, got M=%lld", path,
-                (long long)dfssm::kSkinnyChunkedMaxTokens, (long long)M);
+                (long long)dfssm::kFewPathMaxTokens, (long long)M);
   if (M == 0 || N == 0) return DFSSM_OK;
   st = check_ptrs({{q, "q"}, {s, "s"}, {w_bits, "w_bits"}, {alpha, "alpha"}, {workspace, "workspace"}},
                   {{y, "y"}, {acc_s, "acc_s"}, {acc_a, "acc_a"}, {acc_b, "acc_b"}});
@@ -230,8 +229,8 @@ dfssm_status dfssm_scaffold_lora_linear_ex(const int8_t* q, const float* s, int6
   if (workspace_bytes < need)
     return fail(DFSSM_ERR_WORKSPACE, "workspace %zu bytes < %zu needed", workspace_bytes, need);
   dfssm::LinearWorkspace ws = dfssm::carve_linear_workspace(workspace, M, K, r);
-  hipError_t e = launch_linear(path, q, s, M, K, N, r, w_bits, alpha, A, B, beta, y, acc_s, acc_a, acc_b, ws,
-                               (hipStream_t)stream);
+  hipError_t e = launch_linear(path, q, s, M, K, N, r, w_bits, alpha, A, B, false, beta, y, acc_s, acc_a, acc_b, ws,
+                               nullptr, (hipStream_t)stream);
   return e == hipSuccess ? DFSSM_OK : device_fail(e, "linear launch");
 }
 
@@ -252,9 +251,9 @@ dfssm_status dfssm_scaffold_lora_linear_i4(const int8_t* q, const float* s, int6
   if (path != DFSSM_PATH_AUTO && path != DFSSM_PATH_DECODE && path != DFSSM_PATH_MFMA &&
       path != DFSSM_PATH_MFMA_FEW)
     return fail(DFSSM_ERR_SHAPE, "path=%d", path);
-  if (path == DFSSM_PATH_MFMA_FEW && M > dfssm::kSkinnyChunkedMaxTokens)
+  if (path == DFSSM_PATH_MFMA_FEW && M > dfssm::kFewPathMaxTokens)
     return fail(DFSSM_ERR_UNSUPPORTED, "path=%d takes M <= %lld, got M=%lld", path,
-                (long long)dfssm::kSkinnyChunkedMaxTokens, (long long)M);
+                (long long)dfssm::kFewPathMaxTokens, (long long)M);
   if (M == 0 || N == 0) return DFSSM_OK;
   st = check_ptrs({{q, "q"}, {s, "s"}, {w_bits, "w_bits"}, {alpha, "alpha"}, {workspace, "workspace"}},
                   {{y, "y"}, {acc_s, "acc_s"}, {acc_a, "acc_a"}, {acc_b, "acc_b"}});
@@ -266,8 +265,10 @@ dfssm_status dfssm_scaffold_lora_linear_i4(const int8_t* q, const float* s, int6
   const size_t need = dfssm::linear_i4_workspace_bytes(M, K, N, r);
   if (workspace_bytes < need)
     return fail(DFSSM_ERR_WORKSPACE, "workspace %zu bytes < %zu needed", workspace_bytes, need);
-  const hipError_t e = launch_linear_i4(path, q, s, M, K, N, r, w_bits, alpha, A4, B4, beta, y, acc_s, acc_a,
-                                        acc_b, workspace, (hipStream_t)stream);
+  const hipError_t e =
+      launch_linear(path, q, s, M, K, N, r, w_bits, alpha, A4, B4, true, beta, y, acc_s, acc_a, acc_b,
+                    dfssm::carve_linear_workspace(workspace, M, K, r),
+                    static_cast<char*>(workspace) + dfssm::linear_i4_extra_offset(M, K, r), (hipStream_t)stream);
   return e == hipSuccess ? DFSSM_OK : device_fail(e, "int4 linear launch");
 }
 
@@ -350,8 +351,8 @@ extern "C" dfssm_status dfssm_scaffold_lora_linear_noalloc(const int8_t* q, cons
   if (e == hipSuccess) e = scratch_address(dev, &base);
   if (e != hipSuccess) return device_fail(e, "scratch address");
   dfssm::LinearWorkspace ws = dfssm::carve_linear_workspace(base, M, K, r);
-  e = launch_linear(DFSSM_PATH_AUTO, q, s, M, K, N, r, w_bits, alpha, A, B, beta, y, nullptr, nullptr, nullptr, ws,
-                    hs);
+  e = launch_linear(DFSSM_PATH_AUTO, q, s, M, K, N, r, w_bits, alpha, A, B, false, beta, y, nullptr, nullptr, nullptr,
+                    ws, nullptr, hs);
   return e == hipSuccess ? DFSSM_OK : device_fail(e, "linear launch");
 }
 
@@ -484,14 +485,10 @@ dfssm_status dfssm_chain_run(const dfssm_layer* layers, int n_layers, int64_t M,
       sl = sbuf;
     }
     dfssm::LinearWorkspace ws = dfssm::carve_linear_workspace(base + c.off_lin, M, L.K, L.r);
-    // M <= 4: int4 factors go to the few-token kernel, which reads them packed
-    hipError_t e = L.lora_bits == 4 && L.r > 0
-                       ? dfssm::launch_skinny_linear_i4(ql, sl, M, L.K, L.N, L.r, L.w_bits, L.alpha,
-                                                        reinterpret_cast<const uint8_t*>(L.A),
-                                                        reinterpret_cast<const uint8_t*>(L.B), L.beta, y_cur,
-                                                        nullptr, nullptr, nullptr, ws, hs)
-                       : launch_linear(DFSSM_PATH_AUTO, ql, sl, M, L.K, L.N, L.r, L.w_bits, L.alpha, L.A, L.B,
-                                       L.beta, y_cur, nullptr, nullptr, nullptr, ws, hs);
+    // the automatic path never takes the popcount kernels, so packed int4
+    // factors need no room to be expanded
+    const hipError_t e = launch_linear(DFSSM_PATH_AUTO, ql, sl, M, L.K, L.N, L.r, L.w_bits, L.alpha, L.A, L.B,
+                                       L.lora_bits == 4, L.beta, y_cur, nullptr, nullptr, nullptr, ws, nullptr, hs);
     if (e != hipSuccess) return device_fail(e, "chain linear launch");
     y_prev = y_cur;
     y_cur += M * L.N;
@@ -897,13 +894,8 @@ dfssm_status dfssm_mamba2_decode_step(const dfssm_mamba2_model* model, int64_t M
     if (e != hipSuccess) break;
     const bool i4 = L.lora_bits == 4;
     const dfssm_layer& I = L.in_proj;
-    if (i4)
-      e = launch_linear_i4(DFSSM_PATH_AUTO, w.q, w.s, M, I.K, I.N, I.r, I.w_bits, I.alpha,
-                           reinterpret_cast<const uint8_t*>(I.A), reinterpret_cast<const uint8_t*>(I.B), I.beta,
-                           w.zx, nullptr, nullptr, nullptr, w.lin, hs);
-    else
-      e = launch_linear(DFSSM_PATH_AUTO, w.q, w.s, M, I.K, I.N, I.r, I.w_bits, I.alpha, I.A, I.B, I.beta, w.zx,
-                        nullptr, nullptr, nullptr, dfssm::carve_linear_workspace(w.lin, M, I.K, I.r), hs);
+    e = launch_linear(DFSSM_PATH_AUTO, w.q, w.s, M, I.K, I.N, I.r, I.w_bits, I.alpha, I.A, I.B, i4, I.beta, w.zx,
+                      nullptr, nullptr, nullptr, dfssm::carve_linear_workspace(w.lin, M, I.K, I.r), nullptr, hs);
     if (e != hipSuccess) break;
     // the SSM step applies the gate (y * silu(z), one fp32 product per
     // channel, spread over its workgroups), so the norm after it is a plain
@@ -915,13 +907,8 @@ dfssm_status dfssm_mamba2_decode_step(const dfssm_mamba2_model* model, int64_t M
     e = dfssm::launch_add_rmsnorm_quant(w.y, nullptr, L.gate_w, eps, M, d.d_inner, nullptr, w.q, w.s, hs);
     if (e != hipSuccess) break;
     const dfssm_layer& O = L.out_proj;
-    if (i4)
-      e = launch_linear_i4(DFSSM_PATH_AUTO, w.q, w.s, M, O.K, O.N, O.r, O.w_bits, O.alpha,
-                           reinterpret_cast<const uint8_t*>(O.A), reinterpret_cast<const uint8_t*>(O.B), O.beta,
-                           w.delta, nullptr, nullptr, nullptr, w.lin, hs);
-    else
-      e = launch_linear(DFSSM_PATH_AUTO, w.q, w.s, M, O.K, O.N, O.r, O.w_bits, O.alpha, O.A, O.B, O.beta, w.delta,
-                        nullptr, nullptr, nullptr, dfssm::carve_linear_workspace(w.lin, M, O.K, O.r), hs);
+    e = launch_linear(DFSSM_PATH_AUTO, w.q, w.s, M, O.K, O.N, O.r, O.w_bits, O.alpha, O.A, O.B, i4, O.beta, w.delta,
+                      nullptr, nullptr, nullptr, dfssm::carve_linear_workspace(w.lin, M, O.K, O.r), nullptr, hs);
   }
   if (e == hipSuccess)
     e = dfssm::launch_add_rmsnorm_quant(w.u, w.delta, model->norm_f, eps, M, d.d_model, w.u, w.q, w.s, hs);

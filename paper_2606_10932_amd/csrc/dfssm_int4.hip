@@ -1,5 +1,5 @@
-// dfssm_int4.hip -- expansion of int4 LoRA factors to int8 for the paths
-// that read int8 operands (prefill MFMA, popcount GEMV), gfx950.  A thread
+// dfssm_int4.hip -- expansion of int4 LoRA factors to int8 for the path
+// that reads int8 operands (popcount GEMV), gfx950.  A thread
 // turns 8 packed bytes into 16 values: one 8-byte load, one 16-byte store.
 #include <algorithm>
 

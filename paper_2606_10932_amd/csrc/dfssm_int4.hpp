@@ -1,7 +1,7 @@
 // dfssm_int4.hpp -- the scaffold + LoRA linear with int4 LoRA factors:
 // A4 [r][K/2] and B4 [N][r/2] bytes of two's-complement nibbles, value 2i in
-// the low nibble of byte i.  The few-token kernel reads them directly; the
-// other paths expand them to int8 in the workspace first.
+// the low nibble of byte i.  The MFMA kernels read them directly; the popcount
+// path expands them to int8 in the workspace first.
 #pragma once
 
 #include "dfssm_internal.hpp"
@@ -14,6 +14,13 @@ hipError_t launch_skinny_linear_i4(const int8_t* q, const float* s, int64_t M, i
                                    const uint8_t* A4, const uint8_t* B4, const float* beta, float* y,
                                    int32_t* acc_s, int32_t* acc_a_out, int64_t* acc_b,
                                    const LinearWorkspace& ws, hipStream_t st);
+
+// The split-K tile kernel reading int4 factors.
+hipError_t launch_mid_linear_i4(const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N,
+                                int64_t r, const uint32_t* w_bits, const float* alpha,
+                                const uint8_t* A4, const uint8_t* B4, const float* beta, float* y,
+                                int32_t* acc_s, int32_t* acc_a_out, int64_t* acc_b,
+                                const LinearWorkspace& ws, hipStream_t st);
 
 // n values from packed nibbles to int8 (dst[i] = value i).
 hipError_t launch_unpack_int4(const uint8_t* src, int64_t n, int8_t* dst, hipStream_t st);

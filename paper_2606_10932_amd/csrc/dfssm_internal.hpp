@@ -18,14 +18,6 @@ constexpr int64_t kMaxRank = 256;
 // Largest M the bit-plane decode kernels take in one pass; larger M on the
 // decode path is processed in blocks of this many tokens.
 constexpr int kDecodeMaxTokens = 4;
-// Automatic dispatch: M <= kDecodeM0 uses the popcount decode kernels, M up
-// to kSkinnyMaxTokens the few-token MFMA kernel, larger M the prefill MFMA
-// kernel.  Measured on MI355X, the single-launch few-token kernel is the
-// faster one from one token on (the popcount GEMV needs a second launch for
-// the LoRA down-projection and the bit-planes), so the popcount kernels run
-// on request and inside the persistent chain.
-constexpr int64_t kDecodeM0 = 0;
-
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Test switches (dfssm_test_switch), all 0 unless a test sets them: the
@@ -33,7 +25,8 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 //   local_lora:           1 = the few-token kernel launches no LoRA
 //                         workgroups (every output workgroup computes those
 //                         values itself)
-//   prefill_kernel:       0 = automatic, 4 or 8 = that prefill kernel
+//   prefill_kernel:       0 = automatic, 4 or 8 = the 128 x 128 or the 128 x
+//                         256 tile of the many-token path
 //   lm_head_mfma_tokens:  0 = 8; else the token count from which the LM
 //                         head runs on the matrix cores
 int test_switch(int which);
@@ -68,13 +61,13 @@ struct LinearWorkspace {
 inline int64_t rank_padded(int64_t r) { return round_up(r > 0 ? r : 1, 64); }
 inline int64_t plane_chunks(int64_t K) { return ceil_div(K, 128); }
 
-// Few tokens on the matrix cores: the largest M of the one-launch kernel on
-// request, and of its automatic use.
-constexpr int64_t kSkinnyMaxTokens = 32;
-constexpr int64_t kSkinnyChunkedMaxTokens = 512;
-// Exchange words of the few-token kernel: M*rp limb words, then M sum-Q
-// words, for every M <= kSkinnyChunkedMaxTokens and r <= kMaxRank.
-constexpr int64_t kXwWords = kSkinnyChunkedMaxTokens * kMaxRank + kSkinnyChunkedMaxTokens;
+// Largest M of the few-token kernel, and of DFSSM_PATH_MFMA_FEW on request
+// (the split-K tile kernel above the former).
+constexpr int64_t kSkinnyMaxTokens = 16;
+constexpr int64_t kFewPathMaxTokens = 512;
+// Exchange words of the few-token and the split-K tile kernel: M*rp limb
+// words, then M sum-Q words (M in whole 16-token tiles), for every M <= kFewPathMaxTokens and r <= kMaxRank.
+constexpr int64_t kXwWords = kFewPathMaxTokens * kMaxRank + kFewPathMaxTokens;
 // Epoch words of the few-token kernel (its arrivals spread over them) and
 // their spacing in 64-bit words.
 constexpr int kEpochGroups = 64;
@@ -126,19 +119,28 @@ hipError_t launch_decode_linear(const int8_t* q, const float* s, int64_t M, int6
 // Few tokens (M <= kSkinnyMaxTokens) on the matrix cores, one launch: LoRA
 // workgroups publish acc_a and sum Q as tagged words while the others run a
 // split-K expanded-sign int8 MFMA product over 16 output rows each, then the
-// LoRA up-projection and epilogue.  Above kSkinnyMaxTokens, on request, its
-// output blocks take one chunk of tokens each (a second grid dimension).
+// LoRA up-projection and epilogue.
 hipError_t launch_skinny_linear(const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N,
                                 int64_t r, const uint32_t* w_bits, const float* alpha,
                                 const int8_t* A, const int8_t* B, const float* beta, float* y,
                                 int32_t* acc_s, int32_t* acc_a_out, int64_t* acc_b,
                                 const LinearWorkspace& ws, hipStream_t st);
 
-// MFMA path: LoRA down-projection + limbs + sum Q, then the expanded-sign
-// int8 MFMA GEMM with the LoRA up-projection and epilogue.
-hipError_t launch_mfma_linear(const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N,
+// A few tokens to about a thousand: split-K tiles, LoRA words exchanged in the
+// launch (dfssm_mid.hip).  mid_takes: whether the words of M tokens and rank r
+// fit their region.
+bool mid_takes(int64_t M, int64_t r);
+hipError_t launch_mid_linear(const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N,
+                             int64_t r, const uint32_t* w_bits, const float* alpha,
+                             const int8_t* A, const int8_t* B, const float* beta, float* y,
+                             int32_t* acc_s, int32_t* acc_a_out, int64_t* acc_b,
+                             const LinearWorkspace& ws, hipStream_t st);
+
+// Many tokens: LoRA down-projection, then LDS-staged tiles (dfssm_tile.hip).
+// l4: A and B hold packed int4.
+hipError_t launch_tile_linear(const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N,
                               int64_t r, const uint32_t* w_bits, const float* alpha,
-                              const int8_t* A, const int8_t* B, const float* beta, float* y,
+                              const int8_t* A, const int8_t* B, bool l4, const float* beta, float* y,
                               int32_t* acc_s, int32_t* acc_a_out, int64_t* acc_b,
                               const LinearWorkspace& ws, hipStream_t st);
 
@@ -159,8 +161,10 @@ hipError_t launch_lm_head(const int8_t* q, const float* s, int64_t M, int64_t d,
 // Compute units of the current device (cached per device; 256 if the query
 // fails).
 int device_cu_count();
-// modelled duration (us) of the prefill path for an M x K x N linear
-double prefill_cost_us(int64_t M, int64_t K, int64_t N);
+// Modelled durations (us) of the split-K tile kernel and of the many-token
+// path.
+double mid_cost_us(int64_t M, int64_t K, int64_t N, int64_t r);
+double tile_cost_us(int64_t M, int64_t K, int64_t N);
 
 // ---------------------------------------------------------------- chain
 // The persistent chain kernel (M = 1): one launch of one workgroup per CU

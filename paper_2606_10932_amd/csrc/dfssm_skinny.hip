@@ -1,11 +1,9 @@
-// dfssm_skinny.hip -- scaffold + LoRA linear for a few tokens (M <= 32) on
+// dfssm_skinny.hip -- scaffold + LoRA linear for a few tokens (M <= 16) on
 // the gfx950 int8 matrix cores (v_mfma_i32_16x16x64_i8).
 //
-// At 5..32 tokens the product is still a contraction the matrix cores finish
-// in a fraction of the time the sign bits take to stream, but it has too few
-// token columns for the prefill tiling (128-token tiles, one long K-loop per
-// block).  Here a workgroup owns 16 output rows and every token, and its
-// waves split K:
+// At a few tokens the product is still a contraction the matrix cores finish
+// in a fraction of the time the sign bits take to stream.  Here a workgroup
+// owns 16 output rows and every token, and its waves split K:
 //  * each lane loads, before any arithmetic, 16*S consecutive columns of its
 //    row's sign bits (S = 4: one 8-byte load; S = 8: one 16-byte load) and
 //    the same columns of its token's codes, then runs S MFMAs per 16-token
@@ -16,8 +14,8 @@
 //  * the signs are expanded to {0,1} bytes in registers (nibble n -> bytes
 //    (n * 0x00204081) & 0x01010101), so the MFMA gives D = sum_{bit=1} Q and
 //    acc_s = 2*D - sum_k Q;
-//  * the waves' partial tiles are summed in LDS; one wave per token tile then
-//    does the LoRA up-projection (four limb MFMAs: E_hi = 256*(B.L3) + B.L2,
+//  * the waves' partial tiles are summed in LDS; one wave then does the
+//    LoRA up-projection (four limb MFMAs: E_hi = 256*(B.L3) + B.L2,
 //    E_lo = 256*(B.L1) + B.L0, exact int64 acc_b = E_lo + 65536*E_hi) and the
 //    fp32 epilogue; its row operands were loaded at the start.
 // One launch: the first nb_lora workgroups compute the LoRA down-projection
@@ -47,99 +45,12 @@
 #include <atomic>
 
 #include "dfssm_int4.hpp"
+#include "dfssm_linear.hpp"
 #include "dfssm_persist.hpp"
 
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ v4i mfma(v4i a, v4i b, v4i c) {
-  return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ v4i zero4() { return v4i{0, 0, 0, 0}; }
-
-// bits [sh, sh+16) of w -> 16 bytes of {0,1}, byte b of dword t = bit sh+4t+b
-__device__ __forceinline__ v4i expand16_at(uint32_t w, uint32_t sh) {
-  v4i o;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const uint32_t nib = __builtin_amdgcn_ubfe(w, sh + 4 * t, 4);
-    o[t] = (int)((nib * 0x00204081u) & 0x01010101u);
-  }
-  return o;
-}
-
-__device__ __forceinline__ v4i load16(const int8_t* p) {
-  const uint4 u = *reinterpret_cast<const uint4*>(p);
-  return v4i{(int)u.x, (int)u.y, (int)u.z, (int)u.w};
-}
-
-// 16 bytes of an int8 row, zero outside [0, len)
-__device__ __forceinline__ v4i load16_guarded(const int8_t* row, int start, int len, bool aligned) {
-  if (start + 16 <= len && aligned) return load16(row + start);
-  v4i o = zero4();
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int i = start + e;
-    const uint32_t b = (i >= 0 && i < len) ? (uint32_t)(uint8_t)row[i] : 0u;
-    o[e >> 2] |= (int)(b << (8 * (e & 3)));
-  }
-  return o;
-}
-
-// int4 factors: two's-complement nibbles, value 2i in the low nibble of byte
-// i.  sext_nibbles turns 4 bytes holding nibble values 0..15 into the
-// signed values -8..7 (XOR 8, then a subtraction that cannot borrow across
-// bytes); expand_i4 turns 8 packed bytes into the 16 int8 values in order.
-__device__ __forceinline__ uint32_t sext_nibbles(uint32_t t) {
-  t ^= 0x08080808u;
-  return ((t | 0x80808080u) - 0x08080808u) ^ 0x80808080u;
-}
-
-__device__ __forceinline__ uint4 expand_i4(uint2 p) {
-  const uint32_t lo0 = p.x & 0x0F0F0F0Fu, hi0 = (p.x >> 4) & 0x0F0F0F0Fu;
-  const uint32_t lo1 = p.y & 0x0F0F0F0Fu, hi1 = (p.y >> 4) & 0x0F0F0F0Fu;
-  // v_perm_b32 interleaves the low-nibble and high-nibble bytes
-  return make_uint4(sext_nibbles(__builtin_amdgcn_perm(hi0, lo0, 0x05010400u)),
-                    sext_nibbles(__builtin_amdgcn_perm(hi0, lo0, 0x07030602u)),
-                    sext_nibbles(__builtin_amdgcn_perm(hi1, lo1, 0x05010400u)),
-                    sext_nibbles(__builtin_amdgcn_perm(hi1, lo1, 0x07030602u)));
-}
-
-// values start .. start+15 (start % 16 == 0) of a factor row, in bytes
-// (L4: 8 packed bytes at start/2)
-template <bool L4>
-__device__ __forceinline__ uint4 load_row16(const int8_t* row, int start) {
-  if constexpr (L4) return expand_i4(*reinterpret_cast<const uint2*>(row + start / 2));
-  return *reinterpret_cast<const uint4*>(row + start);
-}
-
-// 16 values of a factor row of len values, zero outside [0, len)
-template <bool L4>
-__device__ __forceinline__ v4i load16_row_guarded(const int8_t* row, int start, int len, bool aligned) {
-  if constexpr (!L4) {
-    return load16_guarded(row, start, len, aligned);
-  } else {
-    if (start + 16 <= len && aligned) {
-      const uint4 u = load_row16<true>(row, start);
-      return v4i{(int)u.x, (int)u.y, (int)u.z, (int)u.w};
-    }
-    v4i o = zero4();
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int i = start + e;
-      uint32_t b = 0u;
-      if (i >= 0 && i < len) {
-        const int byte = (uint8_t)row[i >> 1];
-        const int nib = (i & 1) ? (byte >> 4) : (byte & 15);
-        b = (uint32_t)(uint8_t)(int8_t)(nib >= 8 ? nib - 16 : nib);
-      }
-      o[e >> 2] |= (int)(b << (8 * (e & 3)));
-    }
-    return o;
-  }
-}
+using namespace dfssm_lin;
 
 constexpr int kMaxWaves = 8;
 
@@ -171,10 +82,6 @@ struct SkinnyArgs {
 };
 
 
-__device__ __forceinline__ int sdot4(uint32_t a, uint32_t b, int c) {
-  return __builtin_amdgcn_sdot4((int)a, (int)b, c, false);
-}
-
 // whole-wave sum, the total in every lane (DPP inside 16-lane rows, then
 // gfx950's permlane swaps across rows and halves)
 __device__ __forceinline__ int wave_sum(int v) {
@@ -186,39 +93,6 @@ __device__ __forceinline__ int wave_sum(int v) {
   v = (int)(p[0] + p[1]);
   p = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
   return (int)(p[0] + p[1]);
-}
-
-// agent scope: the words cross XCDs (each XCD has its own L2)
-__device__ __forceinline__ void word_store(uint64_t* p, uint32_t tag, uint32_t v) {
-  __hip_atomic_store(p, ((uint64_t)tag << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint64_t word_load(const uint64_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ uint32_t pack_limbs(int32_t v) {
-  int8_t d[4];
-  dfssm_dev::split_limbs(v, d);
-  return (uint32_t)(uint8_t)d[0] | ((uint32_t)(uint8_t)d[1] << 8) | ((uint32_t)(uint8_t)d[2] << 16) |
-         ((uint32_t)(uint8_t)d[3] << 24);
-}
-
-// sum_k A[j,k] Q[m,k] (j < r) or sum_k Q[m,k] (j < 0), one lane alone
-template <bool L4>
-__device__ int lane_dot(const int8_t* __restrict__ A, const int8_t* __restrict__ q, int K, int j, int m) {
-  const int8_t* qrow = q + (int64_t)m * K;
-  const int8_t* arow = A + (int64_t)(j < 0 ? 0 : j) * (L4 ? K / 2 : K);
-  int acc = 0;
-  for (int k = 0; k < K; k += 16) {
-    const uint4 x = *reinterpret_cast<const uint4*>(qrow + k);
-    const uint4 w = j < 0 ? make_uint4(0x01010101u, 0x01010101u, 0x01010101u, 0x01010101u)
-                          : load_row16<L4>(arow, k);
-    acc = sdot4(w.x, x.x, acc);
-    acc = sdot4(w.y, x.y, acc);
-    acc = sdot4(w.z, x.z, acc);
-    acc = sdot4(w.w, x.w, acc);
-  }
-  return acc;
 }
 
 // LoRA workgroup: wave w takes item b*nw + w = (token group of 4, rank j);
@@ -449,27 +323,27 @@ __device__ void fetch_lora(const SkinnyArgs& a, uint32_t tag, int t0, int j0, in
   if (sq) *sq = (int)vq;
 }
 
-// MT token tiles of 16 (M <= 16*MT); S MFMA steps per lane per iteration;
+// One tile of up to 16 tokens; S MFMA steps per lane per iteration;
 // PM: how the output waves get the LoRA words: 0 from one copy, lane by
 // lane; 1 from their XCD's copy (a.xcopies == 8), the finishing wave alone;
-// 2 (MT == 1) from their XCD's copy, several waves together.
-// Block: 16 output rows, nw = blockDim.x / 64 waves (nw >= MT), wave w takes
+// 2 from their XCD's copy, several waves together.
+// Block: 16 output rows, nw = blockDim.x / 64 waves, wave w takes
 // iterations w, w + nw, ... of 64*S columns each.
-template <int MT, int S, bool L4, int PM>
+template <int S, bool L4, int PM>
 __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
   constexpr bool CP = PM > 0;
-  __shared__ v4i red[kMaxWaves][MT][64];
-  __shared__ __align__(16) uint32_t wx[MT][PM == 2 ? 16 * kWxPitch : (CP ? kCoalTokens * kWxPitch : 4)];
-  __shared__ int wq[MT][PM == 2 ? 16 : (CP ? kCoalTokens : 1)];
+  __shared__ v4i red[kMaxWaves][64];
+  __shared__ __align__(16) uint32_t wx[PM == 2 ? 16 * kWxPitch : (CP ? kCoalTokens * kWxPitch : 4)];
+  __shared__ int wq[PM == 2 ? 16 : (CP ? kCoalTokens : 1)];
   __shared__ int gok[PM == 2 ? kMaxWaves : 1];
   __shared__ uint32_t tag_lds;
   if ((int)blockIdx.x < a.nb_lora) {
-    if (blockIdx.y == 0) lora_block<L4>(a);  // one set of LoRA workgroups for all tokens
+    lora_block<L4>(a);
     return;
   }
   // an output workgroup arrives once, at its start (device-epoch calls); the
   // epoch is needed only after the scaffold product
-  const int member = a.lora_members + (int)blockIdx.y * (int)(gridDim.x - a.nb_lora) + ((int)blockIdx.x - a.nb_lora);
+  const int member = a.lora_members + ((int)blockIdx.x - a.nb_lora);
   uint64_t ep_old = 0;
   if (a.epoch && threadIdx.x == 0) ep_old = dfssm_dev::arrive(a.epoch, member);
   constexpr int KW = 64 * S;  // columns per wave iteration
@@ -480,7 +354,6 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
   const int rho = lane & 15, kg = lane >> 4;
   const int M = a.M, K = a.K, N = a.N, r = a.r, W = K >> 5;
   const int n0 = 16 * ((int)blockIdx.x - a.nb_lora);
-  const int mb = 16 * MT * (int)blockIdx.y;  // first token of this block's chunk (row y of the grid)
   const int nrow = min(n0 + rho, N - 1);  // sign / B row of this lane (rows past N are never stored)
   const uint32_t* wrow = a.w_bits + (int64_t)nrow * W;
   const int nit = (K + KW - 1) / KW;
@@ -488,8 +361,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
 
   // ---- the row operands of the wave that finishes token tile `wave` go
   //      out first: B bytes of ranks 0..63, row scales, token scales
-  const bool fin = wave < MT;
-  const int mtok = mb + 16 * wave + rho;  // token of this lane in the finished tile
+  const bool fin = wave == 0;
+  const int mtok = rho;  // token of this lane
   const int mc = min(mtok, M - 1);
   const int nb = n0 + 4 * kg;  // this lane's output rows nb .. nb+3
   const bool ba = (r % 16) == 0;
@@ -529,9 +402,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
   }
 
   // ---- scaffold: this wave's share of K
-  v4i acc[MT];
-#pragma unroll
-  for (int i = 0; i < MT; ++i) acc[i] = zero4();
+  v4i acc = zero4();
   for (int it = wave; it < nit; it += nw) {
     const int kc = it * KW + kg * 16 * S;  // first column of this lane (a multiple of 64)
     const int wd0 = kc >> 5;
@@ -549,28 +420,19 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
 #pragma unroll
       for (int i = 0; i < SW; ++i) sw[i] = wd0 + i < W ? wrow[wd0 + i] : 0u;
     }
-    v4i x[MT][S];
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      const int m = mb + 16 * i + rho;
-      const int8_t* qrow = a.q + (int64_t)min(m, M - 1) * K;
-#pragma unroll
-      for (int v = 0; v < S; ++v) {
-        const int col = kc + 16 * v;  // K % 32 == 0: 16 columns are wholly in or out
-        x[i][v] = (m < M && col < K) ? load16(qrow + col) : zero4();
-      }
-    }
+    v4i x[S];
+    const int8_t* qrow = a.q + (int64_t)min(rho, M - 1) * K;
 #pragma unroll
     for (int v = 0; v < S; ++v) {
-      const v4i sg = expand16_at(sw[v >> 1], 16 * (v & 1));
-#pragma unroll
-      for (int i = 0; i < MT; ++i) acc[i] = mfma(sg, x[i][v], acc[i]);
+      const int col = kc + 16 * v;  // K % 32 == 0: 16 columns are wholly in or out
+      x[v] = (rho < M && col < K) ? load16(qrow + col) : zero4();
     }
+#pragma unroll
+    for (int v = 0; v < S; ++v) acc = mfma(expand16_at(sw[v >> 1], 16 * (v & 1)), x[v], acc);
   }
 
-  // ---- sum the waves' partial tiles; wave i finishes token tile i
-#pragma unroll
-  for (int i = 0; i < MT; ++i) red[wave][i][lane] = acc[i];
+  // ---- sum the waves' partial tiles; wave 0 finishes the tile
+  red[wave][lane] = acc;
   if (threadIdx.x == 0) {
     if (a.epoch) {
       tag_lds = dfssm_dev::epoch_tag(ep_old);
@@ -586,15 +448,15 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
   // rows, and all meet at a barrier (one wave holding 16 tokens' loads
   // would take 31 more VGPRs)
   int pre = 0;
-  if constexpr (PM == 2 && MT == 1) {
+  if constexpr (PM == 2) {
     {
       constexpr int G = L4 ? 2 : kCoalTokens;
-      const int ntk = max(1, min(16, M - mb));
+      const int ntk = min(16, M);
       const int ng = (ntk + G - 1) / G;  // <= nw (host)
       if (wave < ng) {
         const uint64_t* xc = a.xw + (int64_t)dfssm_px::xcc_id() * a.xstride;
         const int t = G * wave, n = min(G, ntk - t);
-        const bool ok = poll_tokens<G>(a, tag, xc, mb + t, n, 0, true, wx[0] + t * kWxPitch, wq[0] + t);
+        const bool ok = poll_tokens<G>(a, tag, xc, t, n, 0, true, wx + t * kWxPitch, wq + t);
         if (lane == 0) gok[wave] = ok ? 1 : 0;
       }
       __syncthreads();
@@ -604,8 +466,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
     }
   }
   if (!fin) return;
-  v4i d = red[0][wave][lane];
-  for (int w = 1; w < nw; ++w) d += red[w][wave][lane];
+  v4i d = red[0][lane];
+  for (int w = 1; w < nw; ++w) d += red[w][lane];
 
   // LoRA limbs of ranks 0..63 and sum Q of this lane's token; the first
   // block of each tile row also keeps acc_a for the caller if its words had
@@ -613,7 +475,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
   v4i lm[4];
   int sq = 0;
   const bool keep = (int)blockIdx.x == a.nb_lora && mtok < M;
-  fetch_lora<L4, CP>(a, tag, mb + 16 * wave, 0, rho, kg, wx[wave], wq[wave], lm, &sq, keep, pre);
+  fetch_lora<L4, CP>(a, tag, 0, 0, rho, kg, wx, wq, lm, &sq, keep, pre);
 
   // LoRA up-projection, limbs 3, 2, 1, 0 over the 64-rank chunks
   if (L4 && bpacked) {
@@ -633,7 +495,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
     for (int j0 = 64; j0 < a.rp; j0 += 64) {
       const v4i bl = load16_row_guarded<L4>(a.B + (int64_t)nrow * bpitch, j0 + 16 * kg, r, ba);
       v4i lj[4];
-      fetch_lora<L4, CP>(a, tag, mb + 16 * wave, j0, rho, kg, wx[wave], wq[wave], lj, nullptr, keep, 0);
+      fetch_lora<L4, CP>(a, tag, 0, j0, rho, kg, wx, wq, lj, nullptr, keep, 0);
       e3 = mfma(bl, lj[3], e3);
       e2 = mfma(bl, lj[2], e2);
       e1 = mfma(bl, lj[1], e1);
@@ -667,31 +529,14 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
   }
 }
 
-template <int MT, int S, bool L4, int PM>
-hipError_t launch_t(const SkinnyArgs& a, int nw, hipStream_t st) {
-  // x: LoRA workgroups then 16-row output blocks; y: 32-token chunks
-  const int64_t blocks = a.nb_lora + dfssm::ceil_div(a.N, 16);
-  const int64_t chunks = dfssm::ceil_div(a.M, 16 * MT);
-  mfma_skinny<MT, S, L4, PM><<<dim3((unsigned)blocks, (unsigned)chunks), dim3(64 * nw), 0, st>>>(a);
-  return hipGetLastError();
-}
-
-// the copy forms (PM > 0) are taken at M <= 8: one token tile
 template <bool L4, int PM>
-hipError_t launch_tiles(const SkinnyArgs& a, int mt, int S, int nw, hipStream_t st) {
-  if (mt == 1) return S == 8 ? launch_t<1, 8, L4, PM>(a, nw, st) : launch_t<1, 4, L4, PM>(a, nw, st);
-  if constexpr (PM == 0) {
-    if (mt == 2) return S == 8 ? launch_t<2, 8, L4, PM>(a, nw, st) : launch_t<2, 4, L4, PM>(a, nw, st);
-    return launch_t<4, 4, L4, PM>(a, nw, st);
-  }
-  return hipErrorInvalidValue;
-}
-
-// Tag of a call enqueued outside graph capture: a process-wide counter with
-// bit 31 set, so it never equals a device-epoch tag (below 2^31) or 0.
-uint32_t host_tag() {
-  static std::atomic<uint32_t> seq{0};
-  return 0x80000000u | (seq.fetch_add(1, std::memory_order_relaxed) & 0x7fffffffu);
+hipError_t launch_t(const SkinnyArgs& a, int S, int nw, hipStream_t st) {
+  const dim3 grid((unsigned)(a.nb_lora + dfssm::ceil_div(a.N, 16))), block(64 * nw);
+  if (S == 8)
+    mfma_skinny<8, L4, PM><<<grid, block, 0, st>>>(a);
+  else
+    mfma_skinny<4, L4, PM><<<grid, block, 0, st>>>(a);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -707,36 +552,24 @@ hipError_t skinny_impl(const int8_t* q, const float* s, int64_t M, int64_t K, in
                        const dfssm::LinearWorkspace& ws, hipStream_t st) {
   using namespace dfssm;
   if (M == 0 || N == 0) return hipSuccess;
-  if (M > kSkinnyChunkedMaxTokens) return hipErrorInvalidValue;
+  if (M > kSkinnyMaxTokens) return hipErrorInvalidValue;
   const int rp = (int)rank_padded(r);
   // 16-byte sign loads (8 MFMA steps) once K gives 4 waves a full one each:
   // at K = 2048 the 1.3B in_proj's 532 workgroups of 4 waves then fit the
   // chip's slots in one round (8 waves of 8-byte loads would not)
-  // above 32 tokens, output blocks of 64 tokens (4 token tiles, 8-byte sign
-  // loads): each sign operand expanded once feeds 4 tiles (the 1.3B out_proj
-  // at M = 256: 31.8 us against 41.3 with 32-token blocks)
-  const int S = M > 32 ? 4 : (K >= 2048 ? 8 : 4);
-  const int mt = M > 32 ? 4 : (M > 16 ? 2 : 1);
-  const int64_t nit = ceil_div(K, 64 * S);
-  const int nw = (int)std::max<int64_t>(mt, std::min<int64_t>(kMaxWaves, nit));
+  const int S = K >= 2048 ? 8 : 4;
+  const int nw = (int)std::min<int64_t>(kMaxWaves, ceil_div(K, 64 * S));
   // Test switch local_lora: no LoRA workgroups, every lane computes its LoRA
   // values itself at once (the path a lane takes when the words never
   // arrive).
   const bool local_only = test_switch(DFSSM_TEST_LOCAL_LORA) == 1;
   const int64_t lora_waves = ceil_div(M, kPrepTokens) * rp;
   const int nb_lora = local_only ? 0 : (int)ceil_div(lora_waves, nw);
-  const int64_t out_blocks = ceil_div(N, 16) * ceil_div(M, 16 * mt);
+  const int64_t out_blocks = ceil_div(N, 16);
   const int arrivals = (int)((local_only ? 0 : lora_waves) + out_blocks);
   // the call's tag: under graph capture from the device epoch (a replay
   // moves it on), otherwise from a host counter (no arrivals at all)
-  // (if the query fails, the device epoch, which is right either way; the
-  // failed query's error is cleared so that the launch check does not see it)
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
-    (void)hipGetLastError();
-    cap = hipStreamCaptureStatusActive;
-  }
-  const bool device_epoch = cap != hipStreamCaptureStatusNone;
+  const bool device_epoch = wants_device_epoch(st);
   // One copy of the LoRA words per XCD, each on a 256-byte boundary (no
   // cache line holds words of two copies), when the LoRA down-projection
   // is the longer path (r > 32) at up to kCoalTokens tokens: every output
@@ -755,13 +588,13 @@ hipError_t skinny_impl(const int8_t* q, const float* s, int64_t M, int64_t K, in
   const bool group = rp == 64 && M > gsize && M <= 8 && ceil_div(M, gsize) <= nw;
   const int xcopies = r > 32 && (M <= kCoalTokens || group) && 8 * xstride <= kXwWords ? 8 : 1;
   SkinnyArgs a{q, s, (int)M, (int)K, (int)N, (int)r, rp, w_bits, alpha, A, B, beta, y, acc_s, acc_b,
-               ws.acc_a, ws.xw, xstride, xcopies, device_epoch ? ws.epoch : nullptr, device_epoch ? 0u : host_tag(),
+               ws.acc_a, ws.xw, xstride, xcopies, device_epoch ? ws.epoch : nullptr, device_epoch ? 0u : next_host_tag(),
                arrivals, (int)(local_only ? 0 : lora_waves), nb_lora, local_only ? 0 : (1 << 14)};
   // the two poll forms are separate instantiations: in one kernel their
   // union of registers cost a wave per SIMD and spilled
-  hipError_t e = xcopies == 1 ? launch_tiles<L4, 0>(a, mt, S, nw, st)
-                 : group       ? launch_tiles<L4, 2>(a, mt, S, nw, st)
-                               : launch_tiles<L4, 1>(a, mt, S, nw, st);
+  hipError_t e = xcopies == 1 ? launch_t<L4, 0>(a, S, nw, st)
+                 : group       ? launch_t<L4, 2>(a, S, nw, st)
+                               : launch_t<L4, 1>(a, S, nw, st);
   if (e != hipSuccess) return e;
   if (acc_a_out && r > 0)
     e = hipMemcpyAsync(acc_a_out, ws.acc_a, (size_t)(M * r) * 4, hipMemcpyDeviceToDevice, st);
@@ -771,6 +604,20 @@ hipError_t skinny_impl(const int8_t* q, const float* s, int64_t M, int64_t K, in
 }  // namespace
 
 namespace dfssm {
+
+uint32_t next_host_tag() {
+  static std::atomic<uint32_t> seq{0};
+  return 0x80000000u | (seq.fetch_add(1, std::memory_order_relaxed) & 0x7fffffffu);
+}
+
+bool wants_device_epoch(hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    cap = hipStreamCaptureStatusActive;
+  }
+  return cap != hipStreamCaptureStatusNone;
+}
 
 hipError_t launch_skinny_linear(const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N,
                                 int64_t r, const uint32_t* w_bits, const float* alpha,
