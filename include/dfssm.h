@@ -567,8 +567,9 @@ dfssm_status dfssm_mamba2_status(const dfssm_mamba2_model* model, int64_t M, con
  *   DFSSM_TEST_LM_HEAD_MFMA_TOKENS n > 0: the LM head runs on the matrix
  *                                  cores from n tokens instead of 8
  *   DFSSM_TEST_LM_HEAD_TILED_TOKENS n > 0: on the matrix cores, the tiled
- *                                  kernel (both operands staged in LDS)
- *                                  from n tokens instead of 64
+ *                                  kernels (both operands staged in LDS)
+ *                                  from n tokens instead of 64 (17 where
+ *                                  the table is large)
  *   DFSSM_TEST_STEP_PER_KERNEL     1: the decode step at M = 1 runs the
  *                                  per-kernel sequence on a prepared
  *                                  workspace too; 2: the fused step takes

@@ -36,13 +36,6 @@ int lm_head_mfma_tokens() {
   return v > 0 ? v : 8;
 }
 
-// Tokens from which the matrix-core path runs the tiled kernel (64; the
-// test switch lm_head_tiled_tokens moves it).
-int lm_head_tiled_tokens() {
-  const int v = dfssm::test_switch(DFSSM_TEST_LM_HEAD_TILED_TOKENS);
-  return v > 0 ? v : 64;
-}
-
 // rows per wave visit: 4 KB of the table, or one row when rows are longer
 template <int NC>
 constexpr int rows_per_visit() { return NC >= 4 ? 1 : 4 / NC; }
@@ -272,6 +265,46 @@ __global__ __launch_bounds__(64 * kMfmaMaxWaves) void lm_head_mfma(const int8_t*
   }
 }
 
+// Logits of NJ token tiles of one row tile: sum[j] holds rows row0 .. row0 + 3
+// of token m0 + 16 j, whose scale is sm[j].
+template <int NJ>
+__device__ __forceinline__ void store_logits(const v4i (&sums)[NJ], const float (&sm)[NJ], int row0, int m0, int M,
+                                             const float* __restrict__ scale, int V, bool vec_store,
+                                             float* __restrict__ logits, int32_t* __restrict__ acc_out) {
+  const bool whole = vec_store && row0 + 3 < V;
+  float sc[4];
+  if (whole) {
+    const float4 t = *reinterpret_cast<const float4*>(scale + row0);
+    sc[0] = t.x; sc[1] = t.y; sc[2] = t.z; sc[3] = t.w;
+  } else {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sc[v] = row0 + v < V ? scale[row0 + v] : 0.f;
+  }
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int m = m0 + 16 * j;
+    if (m >= M) continue;
+    const v4i sum = sums[j];
+    if (whole) {
+      const float t0 = sc[0] * (float)sum[0], t1 = sc[1] * (float)sum[1];
+      const float t2 = sc[2] * (float)sum[2], t3 = sc[3] * (float)sum[3];
+      if (logits)
+        *reinterpret_cast<float4*>(logits + (int64_t)m * V + row0) =
+            make_float4(sm[j] * t0, sm[j] * t1, sm[j] * t2, sm[j] * t3);
+      if (acc_out) *reinterpret_cast<int4*>(acc_out + (int64_t)m * V + row0) = make_int4(sum[0], sum[1], sum[2], sum[3]);
+    } else {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if (row0 + v < V) {
+          const float tv = sc[v] * (float)sum[v];
+          if (logits) logits[(int64_t)m * V + row0 + v] = sm[j] * tv;
+          if (acc_out) acc_out[(int64_t)m * V + row0 + v] = sum[v];
+        }
+      }
+    }
+  }
+}
+
 // ---- many tokens, tiled: a GEMM with both operands staged in LDS --------
 // A workgroup (4 waves) owns kTlRows vocabulary rows x TB tokens; wave
 // (wr, wt) = (w & 1, w >> 1) owns rows 64 wr .. +63 (4 row tiles) and
@@ -376,41 +409,9 @@ __global__ __launch_bounds__(kTlThreads, 2) void lm_head_tiled(const int8_t* __r
 #pragma unroll
   for (int j = 0; j < NJ; ++j) sm[j] = s[min(m0 + (TB / 2) * wt + 16 * j + rho, M - 1)];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row0 = v0 + 64 * wr + 16 * i + 4 * kg;
-    const bool whole = vec_store && row0 + 3 < V;
-    float sc[4];
-    if (whole) {
-      const float4 t = *reinterpret_cast<const float4*>(scale + row0);
-      sc[0] = t.x; sc[1] = t.y; sc[2] = t.z; sc[3] = t.w;
-    } else {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) sc[v] = row0 + v < V ? scale[row0 + v] : 0.f;
-    }
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int m = m0 + (TB / 2) * wt + 16 * j + rho;
-      if (m >= M) continue;
-      const v4i sum = acc[i][j];
-      if (whole) {
-        const float t0 = sc[0] * (float)sum[0], t1 = sc[1] * (float)sum[1];
-        const float t2 = sc[2] * (float)sum[2], t3 = sc[3] * (float)sum[3];
-        if (logits)
-          *reinterpret_cast<float4*>(logits + (int64_t)m * V + row0) =
-              make_float4(sm[j] * t0, sm[j] * t1, sm[j] * t2, sm[j] * t3);
-        if (acc_out) *reinterpret_cast<int4*>(acc_out + (int64_t)m * V + row0) = make_int4(sum[0], sum[1], sum[2], sum[3]);
-      } else {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          if (row0 + v < V) {
-            const float tv = sc[v] * (float)sum[v];
-            if (logits) logits[(int64_t)m * V + row0 + v] = sm[j] * tv;
-            if (acc_out) acc_out[(int64_t)m * V + row0 + v] = sum[v];
-          }
-        }
-      }
-    }
-  }
+  for (int i = 0; i < 4; ++i)
+    store_logits<NJ>(acc[i], sm, v0 + 64 * wr + 16 * i + 4 * kg, m0 + (TB / 2) * wt + rho, M, scale, V, vec_store,
+                     logits, acc_out);
 }
 
 template <int TB>
@@ -421,6 +422,180 @@ hipError_t launch_tiled(const int8_t* q, const float* s, int64_t M, int64_t d, c
   lm_head_tiled<TB><<<dim3((unsigned)blocks), dim3(kTlThreads), 0, st>>>(q, s, (int)M, (int)d, E, scale, (int)V, logits,
                                                                          acc, (int)nrb, (int)ntb);
   return hipGetLastError();
+}
+
+// ---- many tokens over a large table: all tokens in one workgroup ---------
+// The table has to come from HBM once, and what bounds that is the bytes of
+// it in flight: token blocks of one row block that run side by side ask for
+// the same lines, so lm_head_tiled keeps half of its ring's E bytes in flight
+// twice.  Here a workgroup (8 waves, one per CU) owns kWdRows rows x 64 NJ
+// tokens (up to 256, every token of a decode batch).  E comes in stages of
+// 128 columns (whole 128-byte lines), three of 28 KB on their way; Q comes
+// from L2 in stages of 64 columns.  A wave's loads complete in order, so the
+// two streams have waves of their own: waves 0..3 load E, waves 4..7 load Q,
+// and neither waits for the other's depth.  224 rows put a 50,280-row table on
+// 225 of the 256 CUs in a single round.  Wave (wr, wt) = (w & 1, w >> 1)
+// owns 7 row tiles x NJ token tiles: 7 + NJ operand reads for 7 NJ MFMAs.
+// E and Q place column 64 st + 16 kg + b in byte b of lane (row, kg) alike.
+constexpr int kWdRI = 7;                  // row tiles per wave
+constexpr int kWdRows = 2 * 16 * kWdRI;   // 224
+constexpr int kWdThreads = 512;
+constexpr int kWdMaxNJ = 4;
+constexpr int kWdER = 4, kWdQR = 3;       // ring slots of E and of Q
+constexpr int kWdStageE = kWdRows * 128;
+
+template <int NJ>
+__global__ __launch_bounds__(kWdThreads, 2) void lm_head_wide(const int8_t* __restrict__ q,
+                                                             const float* __restrict__ s, int M, int d,
+                                                             const int8_t* __restrict__ E,
+                                                             const float* __restrict__ scale, int V,
+                                                             float* __restrict__ logits,
+                                                             int32_t* __restrict__ acc_out, int nrb, int ntb) {
+  constexpr int kStageQ = 4 * NJ * 1024;
+  constexpr int LE = kWdStageE / 4096;  // 1 KB loads (8 rows of 128 bytes) per E wave per stage
+  __shared__ __align__(16) int8_t ring_e[kWdER * kWdStageE];
+  __shared__ __align__(16) int8_t ring_q[kWdQR * kStageQ];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rho = lane & 15, kg = lane >> 4;
+  const int id = (int)blockIdx.x, x = id & 7, k = id >> 3;
+  const int tb = k % ntb, rb = (k / ntb) * 8 + x;
+  if (rb >= nrb) return;
+  const int v0 = rb * kWdRows, m0 = tb * 64 * NJ;
+  const bool ewave = wave < 4;
+  const int w4 = wave & 3;
+  // lane offsets of this wave's loads (rows and tokens past the ends repeat
+  // the last one; their results are not stored): 16-byte chunk c of E row r
+  // goes to position c ^ ((r >> 1) & 7) of its 128 bytes, of Q row t to
+  // position c ^ ((t >> 1) & 3) of its 64
+  uint32_t vo[LE];
+#pragma unroll
+  for (int u = 0; u < LE; ++u) {
+    if (ewave) {
+      const int rl = 8 * (w4 + 4 * u) + (lane >> 3);
+      const int c = (lane & 7) ^ ((rl >> 1) & 7);
+      vo[u] = (uint32_t)min(v0 + rl, V - 1) * (uint32_t)d + 16u * (uint32_t)c;
+    } else {
+      const int tl = 16 * (w4 + 4 * u) + (lane >> 2);  // u < NJ is used
+      const int c = (lane & 3) ^ ((tl >> 1) & 3);
+      vo[u] = (uint32_t)min(m0 + tl, M - 1) * (uint32_t)d + 16u * (uint32_t)c;
+    }
+  }
+  const uint32_t e0 = dfssm_px::lds_addr(ring_e) + (uint32_t)w4 * 1024u;
+  const uint32_t q0 = dfssm_px::lds_addr(ring_q) + (uint32_t)w4 * 1024u;
+  const int ns = d / 64, ne = d / 128;
+  auto issue_e = [&](int es) {
+    const uint32_t to = e0 + (uint32_t)((es % kWdER) * kWdStageE);
+#pragma unroll
+    for (int u = 0; u < LE; ++u) dfssm_px::lds_dma16(vo[u], E + 128 * es, to + 4096u * u);
+  };
+  auto issue_q = [&](int st, int slot) {
+    const uint32_t to = q0 + (uint32_t)(slot * kStageQ);
+#pragma unroll
+    for (int u = 0; u < NJ; ++u) dfssm_px::lds_dma16(vo[u], q + 64 * st, to + 4096u * u);
+  };
+  const int wr = wave & 1, wt = wave >> 1;
+  v4i acc[kWdRI][NJ];
+#pragma unroll
+  for (int i = 0; i < kWdRI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = v4i{0, 0, 0, 0};
+  if (ewave) {
+    for (int es = 0; es < kWdER - 1 && es < ne; ++es) issue_e(es);
+  } else {
+    for (int st = 0; st < kWdQR - 1 && st < ns; ++st) issue_q(st, st);
+  }
+  int cur = 0, nxt = kWdQR - 1;  // Q slots of step st and of step st + 2
+  for (int st = 0; st < ns; ++st) {
+    // the loads of step st are in once only those of the later ones remain;
+    // the barrier shows them to every wave and frees the slots of step st - 1
+    // (of E stage st / 2 - 1 at an even step)
+    if (ewave) {
+      if ((st & 1) == 0) switch (min(ne - 1 - (st >> 1), kWdER - 2)) {
+        case 2: CHAIN_WAIT_VMCNT(2 * LE); break;
+        case 1: CHAIN_WAIT_VMCNT(LE); break;
+        default: CHAIN_WAIT_VMCNT(0); break;
+      }
+    } else if (st + 1 < ns) {
+      CHAIN_WAIT_VMCNT(NJ);
+    } else {
+      CHAIN_WAIT_VMCNT(0);
+    }
+    CHAIN_BARRIER();
+    if (ewave) {
+      if ((st & 1) == 0 && (st >> 1) + kWdER - 1 < ne) issue_e((st >> 1) + kWdER - 1);
+    } else if (st + kWdQR - 1 < ns) {
+      issue_q(st + kWdQR - 1, nxt);
+    }
+    const int8_t* sl = ring_q + cur * kStageQ;
+    const int8_t* se = ring_e + ((st >> 1) % kWdER) * kWdStageE;
+    const int ce = 4 * (st & 1) + kg;
+    v4i b[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int t = 16 * (NJ * wt + j) + rho;
+      b[j] = *reinterpret_cast<const v4i*>(sl + t * 64 + 16 * (kg ^ ((t >> 1) & 3)));
+    }
+#pragma unroll
+    for (int i = 0; i < kWdRI; ++i) {
+      const int r = 16 * (kWdRI * wr + i) + rho;
+      const v4i a = *reinterpret_cast<const v4i*>(se + r * 128 + 16 * (ce ^ ((r >> 1) & 7)));
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b[j], acc[i][j], 0, 0, 0);
+    }
+    cur = cur + 1 == kWdQR ? 0 : cur + 1;
+    nxt = nxt + 1 == kWdQR ? 0 : nxt + 1;
+  }
+  // lane (rho, kg) of tile (i, j) holds D[row 112 wr + 16 i + 4 kg + v][token 16 (NJ wt + j) + rho]
+  const bool vec_store = (V & 3) == 0;
+  float sm[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) sm[j] = s[min(m0 + 16 * (NJ * wt + j) + rho, M - 1)];
+#pragma unroll
+  for (int i = 0; i < kWdRI; ++i) {
+    const int row0 = v0 + 16 * (kWdRI * wr + i) + 4 * kg;
+    store_logits<NJ>(acc[i], sm, row0, m0 + 16 * NJ * wt + rho, M, scale, V, vec_store, logits, acc_out);
+  }
+}
+
+template <int NJ>
+hipError_t launch_wide_n(const int8_t* q, const float* s, int64_t M, int64_t d, const int8_t* E, const float* scale,
+                         int64_t V, float* logits, int32_t* acc, hipStream_t st) {
+  const int64_t nrb = dfssm::ceil_div(V, kWdRows), ntb = dfssm::ceil_div(M, 64 * NJ);
+  const int64_t blocks = dfssm::ceil_div(nrb, 8) * 8 * ntb;
+  lm_head_wide<NJ><<<dim3((unsigned)blocks), dim3(kWdThreads), 0, st>>>(q, s, (int)M, (int)d, E, scale, (int)V, logits,
+                                                                        acc, (int)nrb, (int)ntb);
+  return hipGetLastError();
+}
+
+// Whether lm_head_wide takes these sizes: whole 128-byte lines per row, and
+// its workgroups (one per CU) fill at least 3/4 of the rounds they need.
+// us per call in a graph on a 50,280-row table, the kernel it replaces (below
+// 64 tokens lm_head_mfma, else lm_head_tiled) against this one:
+//   tokens      32          64          128         200         256         512
+//   d = 768     14.1/13.4   12.7/14.9   16.8/17.8   26.8/23.9   30.0/27.6   49.7/49.5
+//   d = 1152    17.9/15.7   15.3/17.0   20.6/20.7   35.8/28.2   44.4/32.1   80.1/59.0
+//   d = 1536    23.5/21.5   24.0/22.5   31.2/26.3   48.8/34.0   54.0/38.0   95.3/68.5
+//   d = 2048    29.8/24.6   28.9/26.4   36.6/30.4   57.0/41.5   65.0/44.5   107.8/81.6
+//   d = 2560    41.9/31.3   37.7/33.7   46.2/38.0   71.1/48.4   78.7/51.5   130.2/96.2
+// At 200 tokens and d = 2048 its 143 MB are 3.5 TB/s; LDS reads and MFMAs of a
+// step, which only partly overlap, bound it there, the table at 64.
+bool wide_fills(int64_t M, int64_t d, int64_t V) {
+  const int64_t wgs = dfssm::ceil_div(V, kWdRows) * dfssm::ceil_div(M, 64 * kWdMaxNJ);
+  const int64_t cus = dfssm::device_cu_count();
+  return d % 128 == 0 && 4 * wgs >= 3 * cus * dfssm::ceil_div(wgs, cus);
+}
+
+// as few token blocks as 256 tokens each allow, evenly filled
+hipError_t launch_wide(const int8_t* q, const float* s, int64_t M, int64_t d, const int8_t* E, const float* scale,
+                       int64_t V, float* logits, int32_t* acc, hipStream_t st) {
+  const int64_t ntb = dfssm::ceil_div(M, 64 * kWdMaxNJ);
+  switch (dfssm::ceil_div(dfssm::ceil_div(M, ntb), 64)) {
+    case 1: return launch_wide_n<1>(q, s, M, d, E, scale, V, logits, acc, st);
+    case 2: return launch_wide_n<2>(q, s, M, d, E, scale, V, logits, acc, st);
+    case 3: return launch_wide_n<3>(q, s, M, d, E, scale, V, logits, acc, st);
+    default: return launch_wide_n<4>(q, s, M, d, E, scale, V, logits, acc, st);
+  }
 }
 
 // MFMA steps per wave for row length d, or 0 when the MFMA kernel does not
@@ -500,14 +675,21 @@ namespace dfssm {
 hipError_t launch_lm_head(const int8_t* q, const float* s, int64_t M, int64_t d, const int8_t* E,
                           const float* scale, int64_t V, float* logits, int32_t* acc, hipStream_t st) {
   if (M == 0 || V == 0) return hipSuccess;
-  // from 8 tokens on the matrix cores (the table read once),
+  // from 8 tokens on the matrix cores (the table read once from HBM),
   // below as GEMV passes of up to 4 tokens
   const int ks = mfma_steps(d);
   if (M >= lm_head_mfma_tokens() && ks > 0) {
-    // from 64 tokens the tiled kernel (its load offsets are 32-bit)
-    if (M >= lm_head_tiled_tokens() && V * d < (int64_t)1 << 31 && M * d < (int64_t)1 << 31)
+    // from 64 tokens, or 17 where the table is large, a tiled kernel (the load
+    // offsets of both are 32-bit)
+    const bool fills = wide_fills(M, d, V);
+    const int forced = dfssm::test_switch(DFSSM_TEST_LM_HEAD_TILED_TOKENS);
+    if (M >= (forced > 0 ? forced : fills ? 17 : 64) && V * d < (int64_t)1 << 31 && M * d < (int64_t)1 << 31) {
+      // up to 64 tokens and below 1536 columns a stage of 14 KB of E is too
+      // short a pass for one workgroup per CU: 64-token tiles there
+      if (fills && (M > 64 || d >= 1536)) return launch_wide(q, s, M, d, E, scale, V, logits, acc, st);
       return M >= 128 ? launch_tiled<128>(q, s, M, d, E, scale, V, logits, acc, st)
                       : launch_tiled<64>(q, s, M, d, E, scale, V, logits, acc, st);
+    }
     switch (ks) {
       case 1: return launch_mfma<1>(q, s, M, d, E, scale, V, logits, acc, st);
       case 2: return launch_mfma<2>(q, s, M, d, E, scale, V, logits, acc, st);

@@ -214,3 +214,23 @@ def test_embed_gather_ids_outside_table(env):
     torch.cuda.synchronize()
     assert np.array_equal(x[ok].view(np.uint32), xr.view(np.uint32))
     assert np.all(x[~ok].view(np.uint32) == 0)
+
+
+@pytest.mark.parametrize("M,d,V", [
+    (17, 1536, 43009),   # the fewest tokens; 193 row blocks, the last of one row; V % 4 != 0
+    (64, 1536, 43008),   # one full token block of 64, every row block full
+    (65, 256, 43010),    # two token tiles per wave, the second block row of one token; 2 table stages
+    (129, 384, 43012),   # three; 3 table stages, as many as are in flight
+    (200, 640, 43009),   # four, the last wave partly filled; the ring wraps
+    (256, 512, 43009),   # four, all filled
+    (257, 256, 43009),   # two token blocks
+    (33, 768, 43009),    # few columns: 64-token tiles
+    (70, 320, 43009),    # rows that are no whole 128-byte lines: tiled kernel
+])
+def test_lm_head_large_table(env, M, d, V):
+    # a table large enough for the workgroups that take every token
+    torch, D, o = env
+    say(f"lm_head large table M={M} d={d} V={V}")
+    E, scale = S.embedding(V, d, key=(53, d, V))
+    q, s = o.quantize_act(S.activations(M, d, key=(53, M, d)))
+    _check_lm(torch, D, o, q, s, E, scale, f"M={M} d={d} V={V}")
