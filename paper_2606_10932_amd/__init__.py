@@ -165,14 +165,24 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream(stream=None) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    # the current stream's handle, without building a Stream object for it
+    C = _torch()._C
+    return C._cuda_getCurrentRawStream(C._cuda_getDevice())
+
+
+def _new(like, shape, dtype):
+    """An uninitialised plain tensor on like's device; new_empty skips the
+    keyword handling that makes torch.empty the dearer call."""
     torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if type(like) is torch.Tensor:
+        return like.new_empty(shape, dtype=dtype)
+    return torch.empty(shape, dtype=dtype, device=like.device)
 
 
 def _need(t, dtype, name, ndim=None):
-    torch = _torch()
-    if t is None:
+    if t is None or (t.is_cuda and t.dtype is dtype and t.is_contiguous() and (ndim is None or t.ndim == ndim)):
         return
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
@@ -180,9 +190,7 @@ def _need(t, dtype, name, ndim=None):
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if ndim is not None and t.dim() != ndim:
-        raise ValueError(f"{name} must be {ndim}-D")
-    del torch
+    raise ValueError(f"{name} must be {ndim}-D")
 
 
 def linear_workspace_bytes(M: int, K: int, N: int, r: int) -> int:
@@ -210,8 +218,8 @@ def quantize_act(x, K: Optional[int] = None, q=None, s=None, stream=None):
     M, ldx = x.shape[0], x.stride(0) if x.shape[0] > 1 else x.shape[1]
     K = x.shape[1] if K is None else K
     dt = {torch.float16: F16, torch.float32: F32}[x.dtype]
-    q = torch.empty((M, K), dtype=torch.int8, device=x.device) if q is None else q
-    s = torch.empty((M,), dtype=torch.float32, device=x.device) if s is None else s
+    q = _new(x, (M, K), torch.int8) if q is None else q
+    s = _new(x, (M,), torch.float32) if s is None else s
     _need(q, torch.int8, "q", 2)
     _need(s, torch.float32, "s", 1)
     _check(lib.dfssm_quantize_act(x.data_ptr(), dt, M, K, ldx, q.data_ptr(), s.data_ptr(), _stream(stream)))
@@ -242,15 +250,15 @@ def scaffold_lora_linear(q, s, w_bits, alpha, A=None, B=None, beta=None, y=None,
         if tuple(A.shape) != (r, K) or tuple(B.shape) != (N, r):
             raise ValueError("A must be [r,K] and B [N,r]")
     dev = q.device
-    y = torch.empty((M, N), dtype=torch.float32, device=dev) if y is None else y
+    y = _new(q, (M, N), torch.float32) if y is None else y
     _need(y, torch.float32, "y", 2)
     if workspace is None:
         workspace = linear_workspace(M, K, N, r, device=dev)
     acc_s = acc_a = acc_b = None
     if acc:
-        acc_s = torch.empty((M, N), dtype=torch.int32, device=dev)
-        acc_a = torch.empty((M, max(r, 1)), dtype=torch.int32, device=dev)
-        acc_b = torch.empty((M, N), dtype=torch.int64, device=dev)
+        acc_s = _new(q, (M, N), torch.int32)
+        acc_a = _new(q, (M, max(r, 1)), torch.int32)
+        acc_b = _new(q, (M, N), torch.int64)
     st = lib.dfssm_scaffold_lora_linear_ex(
         q.data_ptr(), s.data_ptr(), M, K, N, r, w_bits.data_ptr(), alpha.data_ptr(),
         _ptr(A) if r else None, _ptr(B) if r else None, _ptr(beta) if r else None, y.data_ptr(),
@@ -379,7 +387,7 @@ def embed_gather(E, scale, tok, x=None, stream=None):
     _need(tok, torch.int32, "tok", 1)
     V, d = E.shape
     M = tok.shape[0]
-    x = torch.empty((M, d), dtype=torch.float32, device=E.device) if x is None else x
+    x = _new(E, (M, d), torch.float32) if x is None else x
     _need(x, torch.float32, "x", 2)
     if tuple(x.shape) != (M, d) or scale.shape[0] != V:
         raise ValueError("x must be [M, d] and scale [V]")
@@ -401,9 +409,9 @@ def lm_head(q, s, E, scale, logits=None, acc: bool = False, stream=None):
     V = E.shape[0]
     if E.shape[1] != d or scale.shape[0] != V or s.shape[0] != M:
         raise ValueError("E must be [V, d], scale [V] and s [M]")
-    logits = torch.empty((M, V), dtype=torch.float32, device=q.device) if logits is None else logits
+    logits = _new(q, (M, V), torch.float32) if logits is None else logits
     _need(logits, torch.float32, "logits", 2)
-    a = torch.empty((M, V), dtype=torch.int32, device=q.device) if acc else None
+    a = _new(q, (M, V), torch.int32) if acc else None
     _check(lib.dfssm_lm_head(q.data_ptr(), s.data_ptr(), M, d, E.data_ptr(), scale.data_ptr(), V,
                              logits.data_ptr(), _ptr(a), _stream(stream)))
     return (logits, a) if acc else logits
@@ -418,8 +426,8 @@ def add_rmsnorm_quant(u, w, eps: float = 1e-5, delta=None, u_out=None, q=None, s
     _need(delta, torch.float32, "delta", 2)
     _need(u_out, torch.float32, "u_out", 2)
     M, d = u.shape
-    q = torch.empty((M, d), dtype=torch.int8, device=u.device) if q is None else q
-    s = torch.empty((M,), dtype=torch.float32, device=u.device) if s is None else s
+    q = _new(u, (M, d), torch.int8) if q is None else q
+    s = _new(u, (M,), torch.float32) if s is None else s
     _need(q, torch.int8, "q", 2)
     _need(s, torch.float32, "s", 1)
     _check(lib.dfssm_add_rmsnorm_quant(u.data_ptr(), _ptr(delta), w.data_ptr(), float(eps), M, d, _ptr(u_out),
@@ -439,8 +447,8 @@ def gate_norm_quant(y, z, w, eps: float = 1e-5, q=None, s=None, stream=None):
     if tuple(z.shape) != (M, d):
         raise ValueError("z must have y's shape")
     ldz = z.stride(0) if M > 1 else max(z.stride(0), d)   # a single row's stride may be reported as anything
-    q = torch.empty((M, d), dtype=torch.int8, device=y.device) if q is None else q
-    s = torch.empty((M,), dtype=torch.float32, device=y.device) if s is None else s
+    q = _new(y, (M, d), torch.int8) if q is None else q
+    s = _new(y, (M,), torch.float32) if s is None else s
     _check(lib.dfssm_gate_norm_quant(y.data_ptr(), z.data_ptr(), ldz, w.data_ptr(), float(eps), M, d, q.data_ptr(),
                                      s.data_ptr(), _stream(stream)))
     return q, s
@@ -459,7 +467,7 @@ def ssm_step(zxbcdt, step: int, conv_ring, ssm_state, conv_w, conv_b, dt_bias, A
     for t, n in ((conv_ring, "conv_ring"), (ssm_state, "ssm_state"), (conv_w, "conv_w"), (conv_b, "conv_b"),
                  (dt_bias, "dt_bias"), (A_log, "A_log"), (D, "D")):
         _need(t, torch.float32, n)
-    y = torch.empty((M, d_inner), dtype=torch.float32, device=zxbcdt.device) if y is None else y
+    y = _new(zxbcdt, (M, d_inner), torch.float32) if y is None else y
     _need(y, torch.float32, "y", 2)
     _need(xbc, torch.float32, "xbc", 2)
     _check(lib.dfssm_ssm_step(zxbcdt.data_ptr(), ld, M, d_inner, d_state, headdim, int(step), conv_ring.data_ptr(),
@@ -545,7 +553,7 @@ class Mamba2:
         torch = _torch()
         _need(tok, torch.int32, "tok", 1)
         M = tok.shape[0]
-        logits = torch.empty((M, self.vocab), dtype=torch.float32, device=tok.device) if logits is None else logits
+        logits = _new(tok, (M, self.vocab), torch.float32) if logits is None else logits
         _check(lib.dfssm_mamba2_decode_step(ctypes.byref(self.struct), M, tok.data_ptr(), int(step),
                                             conv_ring.data_ptr(), ssm_state.data_ptr(), logits.data_ptr(),
                                             workspace.data_ptr(), workspace.numel(), _stream(stream)))
@@ -582,15 +590,15 @@ def scaffold_lora_linear_i4(q, s, w_bits, alpha, A4=None, B4=None, beta=None, y=
         if tuple(A4.shape) != (r, K // 2) or tuple(B4.shape) != (N, r // 2):
             raise ValueError("A4 must be [r, K/2] and B4 [N, r/2] bytes")
     dev = q.device
-    y = torch.empty((M, N), dtype=torch.float32, device=dev) if y is None else y
+    y = _new(q, (M, N), torch.float32) if y is None else y
     nbytes = int(lib.dfssm_linear_i4_workspace_bytes(M, K, N, r))
     if workspace is None:
         workspace = torch.zeros(max(nbytes, 1), dtype=torch.uint8, device=dev)
     acc_s = acc_a = acc_b = None
     if acc:
-        acc_s = torch.empty((M, N), dtype=torch.int32, device=dev)
-        acc_a = torch.empty((M, max(r, 1)), dtype=torch.int32, device=dev)
-        acc_b = torch.empty((M, N), dtype=torch.int64, device=dev)
+        acc_s = _new(q, (M, N), torch.int32)
+        acc_a = _new(q, (M, max(r, 1)), torch.int32)
+        acc_b = _new(q, (M, N), torch.int64)
     _check(lib.dfssm_scaffold_lora_linear_i4(
         q.data_ptr(), s.data_ptr(), M, K, N, r, w_bits.data_ptr(), alpha.data_ptr(), _ptr(A4) if r else None,
         _ptr(B4) if r else None, _ptr(beta) if r else None, y.data_ptr(), path, _ptr(acc_s),
