@@ -42,17 +42,77 @@ __device__ __forceinline__ int8_t code(float v, float inv) {
   return (int8_t)(int)r;
 }
 
-template <int W>
-__device__ __forceinline__ double sum_lanes(double v) {
-#pragma unroll
-  for (int off = W / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, W);
-  return v;
+// Lane exchanges on the vector ALU (DPP inside 16-lane rows, gfx950's
+// permlane swaps across them): a shuffle by address goes through the LDS
+// pipe, two round trips per fp64 value.
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
 }
 
-__device__ __forceinline__ float max_lanes(float v) {
+// v of lane ^ OFF, OFF = 1, 2, 4 or 8
+template <int OFF>
+__device__ __forceinline__ int lane_xor(int v) {
+  static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8, "inside a row");
+  if constexpr (OFF == 1) return dpp<0xB1>(v);        // quad_perm [1,0,3,2]
+  else if constexpr (OFF == 2) return dpp<0x4E>(v);   // quad_perm [2,3,0,1]
+  else if constexpr (OFF == 4) return dpp<0x1B>(dpp<0x141>(v));  // row_half_mirror (^ 7), quad_perm [3,2,1,0] (^ 3)
+  else return dpp<0x128>(v);                          // row_ror:8
+}
+
+template <int OFF>
+__device__ __forceinline__ double lane_xor(double v) {
+  return __hiloint2double(lane_xor<OFF>(__double2hiint(v)), lane_xor<OFF>(__double2loint(v)));
+}
+
+// lanes with bit OFF clear: a + a of lane ^ OFF; the others: b + b of lane ^ OFF
+template <int OFF>
+__device__ __forceinline__ double fold_pair(double a, double b, int lane) {
+  if constexpr (OFF >= 16) {
+    // the swap exchanges a's upper with b's lower rows (halves), which leaves
+    // the two terms of each lane's sum in its own two registers
+    const unsigned al = __double2loint(a), ah = __double2hiint(a), bl = __double2loint(b), bh = __double2hiint(b);
+    if constexpr (OFF == 16) {
+      const auto lo = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+      const auto hi = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+      return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    } else {
+      const auto lo = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+      const auto hi = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+      return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    }
+  } else {
+    const bool up = (lane & OFF) != 0;
+    return (up ? b : a) + lane_xor<OFF>(up ? a : b);
+  }
+}
+
+// Sums of J values over L lanes, all at once: each step halves the values a
+// lane holds until one is left, whose index is lane / (L / J) of the L lanes.
+// Every sum pairs lanes by L / 2, L / 4, .. 1, whatever J is.
+template <int L, int J>
+__device__ __forceinline__ double sum_lanes(const double (&v)[J], int lane) {
+  if constexpr (L == 1) {
+    return v[0];
+  } else {
+    constexpr int H = J > 1 ? J / 2 : 1;
+    double w[H];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  return v;
+    for (int i = 0; i < H; ++i) w[i] = fold_pair<L / 2>(v[i], v[J > 1 ? i + H : i], lane);
+    return sum_lanes<L / 2, H>(w, lane);
+  }
+}
+
+__device__ __forceinline__ float max_lanes(float f) {
+  int v = __float_as_int(f);  // not negative: ordered as its bits
+  v = max(v, lane_xor<1>(v));
+  v = max(v, lane_xor<2>(v));
+  v = max(v, dpp<0x141>(v));
+  v = max(v, dpp<0x140>(v));  // row_mirror
+  auto p = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+  v = max((int)p[0], (int)p[1]);
+  p = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+  return __int_as_float(max((int)p[0], (int)p[1]));
 }
 
 // ---------------------------------------------------------------- norms
@@ -118,7 +178,8 @@ __global__ __launch_bounds__(kNormMaxThreads) void norm_quant(NormArgs a) {
     ss += (double)g[i].z * (double)g[i].z;
     ss += (double)g[i].w * (double)g[i].w;
   }
-  ss = sum_lanes<64>(ss);
+  const double part[1] = {ss};
+  ss = sum_lanes<64, 1>(part, tid & 63);
   if ((tid & 63) == 0) red_ss[tid >> 6] = ss;
   __syncthreads();
   ss = 0.0;
@@ -207,7 +268,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // The state is read once and written once per step, 4 MB per sequence:
 // non-temporal accesses keep it from displacing the step's shared inputs
-// in the caches (batch 512: 406 us against 434 with plain accesses).
+// in the caches (measured at batch 512 with the loads before the convolution:
+// 406 us against 434 with plain accesses).
 __device__ __forceinline__ f32x4 load_state(const f32x4* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ void store_state(f32x4 v, f32x4* p) { __builtin_nontemporal_store(v, p); }
 
@@ -216,7 +278,10 @@ __device__ __forceinline__ void store_state(f32x4 v, f32x4* p) { __builtin_nonte
 // float4 j NT + t of that block: channel (j NT + t) / L and state columns
 // 4 (t % L) .. + 3, with L = N / 4 lanes per channel, so every load and
 // store of a wave covers 1 KB in one piece; the L lanes of a channel sum
-// y[p] over the state.
+// y[p] over the state, all J channels at once.
+// HBM bounds it: 2 x 512 N bytes of state per head.  At 32 sequences of 64
+// heads (134 MB) 29.9 -> 24.4 us, 5.5 TB/s, and at 256 195 -> 178 us, 6.0 TB/s,
+// with the convolution under the state's loads and the sums off the LDS pipe.
 template <int N, int PB, int NT = kSsmThreads>
 __global__ __launch_bounds__(NT) void ssm_step(SsmArgs a) {
   constexpr int L = N / 4;               // lanes per channel
@@ -234,7 +299,31 @@ __global__ __launch_bounds__(NT) void ssm_step(SsmArgs a) {
   const int conv_dim = a.d_inner + 2 * N;
   const float* zr = a.zx + m * a.ld;
 
-  // the state first: it is the bytes that come from HBM
+  // The convolution's and dt's inputs first, then the state: loads complete
+  // in order, so the convolution and its fp64 exponentials run while the
+  // state, which is the bytes, is on its way.
+  const float* ring_m = a.ring + m * 4 * (int64_t)conv_dim;
+  const int s0 = (int)((a.step + 1) & 3), s1 = (int)((a.step + 2) & 3), s2 = (int)((a.step + 3) & 3);
+  const int sw = (int)(a.step & 3);
+  constexpr int CH = PB + 2 * N;              // channels: this workgroup's, then B and C
+  constexpr int CI = (CH + NT - 1) / NT;
+  float cin[CI], r0[CI], r1[CI], r2[CI], cb[CI];
+  float4 cw[CI];
+#pragma unroll
+  for (int u = 0; u < CI; ++u) {
+    const int i = tid + u * NT;
+    const bool in = i < CH;
+    const int c = !in ? 0 : i < PB ? h * kHeadDim + p0 + i : a.d_inner + (i - PB);
+    cin[u] = in ? zr[a.d_inner + c] : 0.f;
+    r0[u] = in ? ring_m[s0 * (int64_t)conv_dim + c] : 0.f;
+    r1[u] = in ? ring_m[s1 * (int64_t)conv_dim + c] : 0.f;
+    r2[u] = in ? ring_m[s2 * (int64_t)conv_dim + c] : 0.f;
+    cb[u] = in ? a.conv_b[c] : 0.f;
+    cw[u] = in ? *reinterpret_cast<const float4*>(a.conv_w + 4 * (int64_t)c) : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  const float zv = (tid < PB && a.gate_y) ? zr[h * kHeadDim + p0 + tid] : 0.f;
+  const float dt_in = zr[a.d_inner + conv_dim + h], dt_b = a.dt_bias[h], A_l = a.A_log[h], Dh = a.D[h];
+
   f32x4* hs = reinterpret_cast<f32x4*>(a.state + ((m * a.H + h) * kHeadDim + p0) * (int64_t)N) + tid;
   f32x4 hv[J];
 #pragma unroll
@@ -246,30 +335,30 @@ __global__ __launch_bounds__(NT) void ssm_step(SsmArgs a) {
   __shared__ float dt_s[2];
   const bool owns_bc = (hb == 0);
   float* ring = a.ring + m * 4 * (int64_t)conv_dim;
-  const int s0 = (int)((a.step + 1) & 3), s1 = (int)((a.step + 2) & 3), s2 = (int)((a.step + 3) & 3);
-  const int sw = (int)(a.step & 3);
-  for (int i = tid; i < PB + 2 * N; i += NT) {
-    const int c = i < PB ? h * kHeadDim + p0 + i : a.d_inner + (i - PB);
-    const float in = zr[a.d_inner + c];
-    const float4 w = *reinterpret_cast<const float4*>(a.conv_w + 4 * (int64_t)c);
-    float v = w.x * ring[s0 * (int64_t)conv_dim + c];
-    v = v + w.y * ring[s1 * (int64_t)conv_dim + c];
-    v = v + w.z * ring[s2 * (int64_t)conv_dim + c];
-    v = v + w.w * in;
-    v = v + a.conv_b[c];
-    const float o = silu_f(v);
-    xbc_s[i] = o;
-    if (i < PB && a.gate_y) gz_s[i] = silu_f(zr[c]);
-    if (i < PB || owns_bc) {
-      ring[sw * (int64_t)conv_dim + c] = in;
-      if (a.xbc) a.xbc[m * conv_dim + c] = o;
+#pragma unroll
+  for (int u = 0; u < CI; ++u) {
+    const int i = tid + u * NT;
+    if (i < CH) {
+      const int c = i < PB ? h * kHeadDim + p0 + i : a.d_inner + (i - PB);
+      float v = cw[u].x * r0[u];
+      v = v + cw[u].y * r1[u];
+      v = v + cw[u].z * r2[u];
+      v = v + cw[u].w * cin[u];
+      v = v + cb[u];
+      const float o = silu_f(v);
+      xbc_s[i] = o;
+      if (i < PB && a.gate_y) gz_s[i] = silu_f(zv);
+      if (i < PB || owns_bc) {
+        ring[sw * (int64_t)conv_dim + c] = cin[u];
+        if (a.xbc) a.xbc[m * conv_dim + c] = o;
+      }
     }
   }
   // dt and dA once per workgroup, by the last wave (the one with the least
   // convolution work), through LDS
   if (tid >= NT - 64) {
-    const float dt = softplus_f(zr[a.d_inner + conv_dim + h] + a.dt_bias[h]);
-    const float A = (float)(-exp((double)a.A_log[h]));
+    const float dt = softplus_f(dt_in + dt_b);
+    const float A = (float)(-exp((double)A_l));
     if (tid == NT - 64) {
       dt_s[0] = dt;
       dt_s[1] = (float)exp((double)(dt * A));
@@ -282,10 +371,10 @@ __global__ __launch_bounds__(NT) void ssm_step(SsmArgs a) {
   const float* Cs = xbc_s + PB + N + 4 * nc;
   const float b[4] = {Bs[0], Bs[1], Bs[2], Bs[3]};
   const float cc[4] = {Cs[0], Cs[1], Cs[2], Cs[3]};
+  double ysum[J];
 #pragma unroll
   for (int j = 0; j < J; ++j) {
-    const int p = j * CPJ + pj;
-    const float x = xbc_s[p];
+    const float x = xbc_s[j * CPJ + pj];
     const float dtx = dt * x;
     float e[4] = {hv[j].x, hv[j].y, hv[j].z, hv[j].w};
     double acc = 0.0;
@@ -302,32 +391,34 @@ __global__ __launch_bounds__(NT) void ssm_step(SsmArgs a) {
     o.z = e[2];
     o.w = e[3];
     store_state(o, hs + j * NT);
-    acc = sum_lanes<L>(acc);
-    if (nc == 0) {
-      const int c = h * kHeadDim + p0 + p;
-      float yv = (float)(acc + (double)a.D[h] * (double)x);
-      if (a.gate_y) yv = yv * gz_s[p];
-      a.y[m * a.d_inner + c] = yv;
-    }
+    ysum[j] = acc;
+  }
+  const double acc = sum_lanes<L, J>(ysum, nc);
+  if (nc % (L / J) == 0) {
+    const int p = (nc / (L / J)) * CPJ + pj;
+    float yv = (float)(acc + (double)Dh * (double)xbc_s[p]);
+    if (a.gate_y) yv = yv * gz_s[p];
+    a.y[m * a.d_inner + h * kHeadDim + p0 + p] = yv;
   }
 }
 
 template <int N>
 void launch_ssm_n(const SsmArgs& a, int64_t M, hipStream_t st) {
   // More channels per workgroup amortise the B/C convolution every
-  // workgroup repeats over more state, and leave fewer workgroups: 64
-  // channels (32 KB of state) from 16 sequences, 32 from 5.  Per step of
-  // 48 layers' states in a graph (us per call), 32 / 64 channels: batch
-  // 8: 8.6 / 9.3; 12: 10.8 / 11.2; 16: 16.6 / 13.1; 32: 28.0 / 28.4; 256:
-  // 187 / 182; 512: 375 / 363.  Up to 4 sequences the step is latency and
-  // the 16-channel blocks' shorter per-thread chain wins (batch 1: 4.05 us
-  // against 4.75).
-  if (M <= 4)
-    ssm_step<N, 16><<<dim3((unsigned)(M * a.H * (kHeadDim / 16))), dim3(kSsmThreads), 0, st>>>(a);
-  else if (M < 16)
-    ssm_step<N, 32><<<dim3((unsigned)(M * a.H * (kHeadDim / 32))), dim3(kSsmThreads), 0, st>>>(a);
+  // workgroup repeats over more state, and leave fewer workgroups, so the
+  // line lies by the heads of the call: 64 channels (32 KB of state) from 512,
+  // 32 above 64, 16 where the step is latency alone.  us per call over 48
+  // layers' states in a graph, 16 / 32 / 64 channels: 48 heads 3.27 / 3.41 /
+  // 3.68; 96 3.79 / 3.65 / 3.84; 384 7.18 / 6.19 / 6.88; 512 8.58 / 7.91 /
+  // 7.03; 768 (64 a sequence) 11.7 / 10.9 / 10.4; 2048 29.5 / 24.9 / 24.5;
+  // 16,384 214 / 178 / 178.
+  const int64_t heads = M * a.H;
+  if (heads <= 64)
+    ssm_step<N, 16><<<dim3((unsigned)(heads * (kHeadDim / 16))), dim3(kSsmThreads), 0, st>>>(a);
+  else if (heads < 512)
+    ssm_step<N, 32><<<dim3((unsigned)(heads * (kHeadDim / 32))), dim3(kSsmThreads), 0, st>>>(a);
   else
-    ssm_step<N, 64><<<dim3((unsigned)(M * a.H * (kHeadDim / 64))), dim3(kSsmThreads), 0, st>>>(a);
+    ssm_step<N, 64><<<dim3((unsigned)(heads * (kHeadDim / 64))), dim3(kSsmThreads), 0, st>>>(a);
 }
 
 }  // namespace

@@ -162,6 +162,16 @@ def test_ssm_step(env, M, d_model, N, t0, steps):
     _ssm_run(torch, D, o, M, d_model, N, t0, steps, key=(120, M, d_model, N))
 
 
+# each block of channels (up to 64 heads in all, up to 511, from 512; 32 per
+# sequence) with both state sizes: 1 to 8 sums per lane group folded at once
+@pytest.mark.parametrize("N", [64, 128])
+@pytest.mark.parametrize("M", [2, 3, 15, 16])
+def test_ssm_step_channel_blocks(env, M, N):
+    torch, D, o = env
+    say(f"ssm_step channel blocks M={M} N={N}")
+    _ssm_run(torch, D, o, M, 1024, N, 3, 2, key=(124, M, N))
+
+
 def test_ssm_step_large_step_index(env):
     # the ring position is the step index mod 4, at any size of the index
     torch, D, o = env
