@@ -42,6 +42,23 @@ def test_quantize(env, dtype, M, K, ldx):
     assert np.array_equal(host(s).view(np.uint32), sr.view(np.uint32))
 
 
+# rows held in registers, 1, 2 or 4 16-byte loads per thread, and the first
+# row past each
+@pytest.mark.parametrize("dtype,K", [(dt, k) for dt, cols in ((np.float16, 2048), (np.float32, 1024))
+                                     for n in (1, 2, 4) for k in (cols * n, cols * n + 32)])
+def test_quantize_row_lengths(env, dtype, K):
+    torch, D, o = env
+    say(f"quantize rows {np.dtype(dtype)} K={K}")
+    x = S.activations(5, K, key=(12, K)).astype(dtype)
+    x[1] = 0
+    x[2, -1] = 900.0   # the largest value last
+    qr, sr = o.quantize_act(x)
+    q, s = D.quantize_act(dev(x))
+    torch.cuda.synchronize()
+    assert np.array_equal(host(q), qr)
+    assert np.array_equal(host(s).view(np.uint32), sr.view(np.uint32))
+
+
 def test_quantize_ties_and_subnormals(env):
     torch, D, o = env
     say("quantize ties/subnormals")
