@@ -5,6 +5,7 @@
 #pragma once
 
 #include "dfssm_internal.hpp"
+#include "dfssm_persist.hpp"
 
 namespace dfssm {
 
@@ -150,15 +151,13 @@ __device__ __forceinline__ void limb_operands(const uint32_t (&val)[16], v4i (&l
 }
 
 typedef __attribute__((address_space(3))) void lds_void;
+// direct-to-LDS loads; the LDS address is uniform already, which the compiler
+// may not see
 __device__ __forceinline__ void dma16(uint32_t voff, const void* sbase, uint32_t lds) {
-  lds = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds);  // uniform already; the compiler may not see it
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds)
-               : "memory");
+  dfssm_px::lds_dma16(voff, sbase, (uint32_t)__builtin_amdgcn_readfirstlane((int)lds));
 }
 __device__ __forceinline__ void dma4(uint32_t voff, const void* sbase, uint32_t lds) {
-  lds = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds);
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(sbase), "s"(lds)
-               : "memory");
+  dfssm_px::lds_dma4(voff, sbase, (uint32_t)__builtin_amdgcn_readfirstlane((int)lds));
 }
 // at most n of the wave's vector-memory operations still in flight
 template <int n>

@@ -333,3 +333,30 @@ def test_product_and_oracle_are_separate():
     for p, text in _imports(os.path.join(ROOT, "dfssm_synth")):
         assert "oracle" not in text.replace("imports neither the oracle", ""), p
         assert "paper_2606_10932_amd" not in text, p
+
+
+def _asm_statements(text):
+    """The text inside the parentheses of every asm statement."""
+    for m in re.finditer(r"\basm\s+volatile\s*\(", text):
+        depth, i, quoted = 1, m.end(), False
+        while depth:
+            c = text[i]
+            if c == '"' and text[i - 1] != "\\":
+                quoted = not quoted
+            elif not quoted:
+                depth += {"(": 1, ")": -1}.get(c, 0)
+            i += 1
+        yield text[m.end():i - 1]
+
+
+def test_asm_that_writes_m0_declares_it():
+    """An asm statement that sets M0 (the LDS base of a direct-to-LDS load) has
+    to list it as clobbered: the compiler keeps values of its own there."""
+    found = 0
+    csrc = os.path.join(ROOT, "paper_2606_10932_amd", "csrc")
+    for name in sorted(os.listdir(csrc)):
+        for st in _asm_statements(open(os.path.join(csrc, name)).read()):
+            if re.search(r"\bm0,", st):
+                found += 1
+                assert '"m0"' in st.rsplit(":", 1)[1], f"{name}: {st}"
+    assert found >= 2
