@@ -419,6 +419,9 @@ __global__ __launch_bounds__(64 * KW, TT == 1 ? 4 : 2) void mfma_mid(MidArgs a) 
     d[p] = *reinterpret_cast<const v4i*>(rd);
 #pragma unroll
     for (int u = 1; u < KW; ++u) d[p] += *reinterpret_cast<const v4i*>(rd + u * L::kBytes);
+    // summed before the wait for the LoRA words: left to itself the compiler
+    // keeps all KW terms in registers across it, and spills
+    asm volatile("" : "+v"(d[p]));
   }
   const bool keep = rb == 0 && ft == 0 && a.acc_a_out && mtok < M;  // values computed here go to acc_a_out
   int sq = 0;
@@ -426,17 +429,19 @@ __global__ __launch_bounds__(64 * KW, TT == 1 ? 4 : 2) void mfma_mid(MidArgs a) 
   auto finish_poll = [&](int chunk, bool want_q) {
     const int j0 = 64 * chunk + 16 * kg;
     uint32_t val[16];
-    bool have = false;
-    for (int it = 0;; ++it) {
-      bool ok = !want_q || (uint32_t)(wq >> 32) == tag;
+    auto arrived = [&] {
+      uint32_t other = want_q ? (uint32_t)(wq >> 32) ^ tag : 0u;
       if (j0 < r) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) ok = ok && (uint32_t)(w[e] >> 32) == tag;
+        for (int e = 0; e < 16; ++e) other |= (uint32_t)(w[e] >> 32) ^ tag;
       }
-      have = ok;
-      if (__all(ok) || it >= a.spin) break;
+      return other == 0u;
+    };
+    bool have = arrived();
+    for (int it = 0; !__all(have) && it < a.spin; ++it) {
       __builtin_amdgcn_s_sleep(1);
       poll(chunk, want_q);
+      have = arrived();
     }
 #pragma unroll
     for (int e = 0; e < 16; ++e) val[e] = j0 < r ? (uint32_t)w[e] : 0u;

@@ -360,3 +360,25 @@ def test_asm_that_writes_m0_declares_it():
                 found += 1
                 assert '"m0"' in st.rsplit(":", 1)[1], f"{name}: {st}"
     assert found >= 2
+
+
+def _kernel_spills(so):
+    """{kernel symbol: vector registers it spills} from the metadata of the
+    library's gfx950 code objects (MessagePack maps, keys in order, so a kernel's
+    .name precedes its .vgpr_spill_count)."""
+    blob, out, pos = open(so, "rb").read(), {}, 0
+    key = b".vgpr_spill_count"
+    while (pos := blob.find(key, pos)) >= 0:
+        pos += len(key)
+        n = blob[pos]
+        n = {0xCC: blob[pos + 1], 0xCD: int.from_bytes(blob[pos + 1:pos + 3], "big")}.get(n, n)
+        at = blob.rfind(b"\xa5.name", 0, pos) + 6
+        name = re.match(rb"(?:[\xa0-\xbf]|\xd9.|\xda..)(\w+)", blob[at:at + 400], re.S).group(1).decode()
+        out[name] = n
+    return out
+
+
+def test_no_kernel_spills_vector_registers(dl):
+    spills = _kernel_spills(dl.lib._name)
+    assert any("mfma_mid" in k for k in spills) and any("mfma_tile" in k for k in spills)
+    assert {k: n for k, n in spills.items() if n and "mfma_tile" not in k} == {}
