@@ -286,11 +286,13 @@ __global__ __launch_bounds__(256, 2) void mfma_tile(TileArgs a) {
     } else {
       // word by word: lane i of a load fetches word slot i % 4G of row i / 4G
       constexpr int kR4 = 64 / (4 * G);
+      int nn = n0;
+      asm volatile("" : "+s"(nn));  // offsets formed here, not held through the K loop
 #pragma unroll
       for (int j = 0; j < (kRowsS / kR4 + 3) / 4; ++j) {
         const int r0 = kR4 * (wave + 4 * j), row = r0 + lane / (4 * G);
         const int wd = min(4 * (((lane >> 2) % G) ^ sswz(row)) + (lane & 3), W - 1 - w0);
-        const uint32_t o = (uint32_t)(min(n0 + row, N - 1) - n0) * (uint32_t)W + (uint32_t)wd;
+        const uint32_t o = (uint32_t)(min(nn + row, N - 1) - nn) * (uint32_t)W + (uint32_t)wd;
         if (r0 < kRowsS) dma4(4u * o, wb + w0, sb + (uint32_t)(kSgRow * r0));
       }
     }
@@ -299,9 +301,10 @@ __global__ __launch_bounds__(256, 2) void mfma_tile(TileArgs a) {
     if (k % G == 0) issue_signs(k / G);
     const uint32_t sb = lds0 + slot * kQStage + 1024u * wave;
     if (k == ng - 1 && vlast != 7) {  // uniform: pieces past K re-read the last
+      uint32_t past = 16u * (uint32_t)max(lc - vlast, 0);
+      asm volatile("" : "+v"(past));
 #pragma unroll
-      for (int i = 0; i < kLq; ++i)
-        dma16(qoff[i] - 16u * (uint32_t)max(lc - vlast, 0), qb + 128 * k, sb + 4096u * i);
+      for (int i = 0; i < kLq; ++i) dma16(qoff[i] - past, qb + 128 * k, sb + 4096u * i);
     } else {
 #pragma unroll
       for (int i = 0; i < kLq; ++i) dma16(qoff[i], qb + 128 * k, sb + 4096u * i);
