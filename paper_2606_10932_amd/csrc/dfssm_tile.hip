@@ -68,7 +68,7 @@ __global__ __launch_bounds__(64 * KW, 2) void lora_down(DownArgs a) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) qoff[i] = (uint32_t)(min(m0 + 8 * i + lrow, M - 1) - m0) * (uint32_t)K;
   const int apitch = L4 ? K / 2 : K;
-  const int8_t* ab = a.A + (int64_t)j0 * apitch + (L4 ? 64 : 128) * s0;
+  const int8_t* ab = a.A + (L4 ? 64 : 128) * s0;  // rows from 0: a workgroup may lie wholly past rank r
   auto issue = [&](int k) {
     const uint32_t sb = wl0 + (uint32_t)(k % D) * kStep;
     const int lim = s0 + k == ng - 1 ? vlast : 7;
@@ -78,13 +78,13 @@ __global__ __launch_bounds__(64 * KW, 2) void lora_down(DownArgs a) {
       if constexpr (L4) {
 #pragma unroll
         for (int t = 0; t < RA; ++t) {
-          const int row = min(j0 + 16 * t + (lane >> 2), r - 1) - j0;
+          const int row = min(j0 + 16 * t + (lane >> 2), r - 1);
           dma16((uint32_t)(row * apitch) + 16u * min(lane & 3, lim >> 1), ab + 64 * k, sb + 2048u + 1024u * t);
         }
       } else {
 #pragma unroll
         for (int t = 0; t < 2 * RA; ++t) {
-          const int row = min(j0 + 8 * t + lrow, r - 1) - j0;
+          const int row = min(j0 + 8 * t + lrow, r - 1);
           dma16((uint32_t)(row * apitch) + 16u * min(lc, lim), ab + 128 * k, sb + 2048u + 1024u * t);
         }
       }
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(64 * KW, 2) void lora_down(DownArgs a) {
   }
   __syncthreads();
   const int m = m0 + rho;
-  if (RA < 4 && r > 0 && wave >= RA && wave < 4 && m < M) {
+  if (RA == 1 && r > 0 && wave >= RA && wave < 4 && m < M) {
     // ranks 16 .. 63 of the padded rank: zero limbs
 #pragma unroll
     for (int l = 0; l < 4; ++l)
@@ -598,11 +598,17 @@ TilePlan plan_tile(int64_t M, int64_t K, int64_t N) {
   return p;
 }
 
+// 16 ranks per workgroup up to rank 16 (the whole rank), 64 above, or 32 while
+// workgroups of 64 would leave half the CUs without one: us at r = 64 with 64 /
+// 32 ranks, 1000 x 2048 4.2 / 2.7, 1536 x 1024 4.2 / 3.0, 3000 x 4096 7.6 / 9.3,
+// 7001 x 2560 11.9 / 14.8.
 template <bool L4>
 hipError_t launch_down(const DownArgs& a, hipStream_t st) {
   const unsigned mb = (unsigned)dfssm::ceil_div(a.M, 16);
   if (a.r <= 16)
     lora_down<1, 8, L4><<<dim3(mb), dim3(512), 0, st>>>(a);
+  else if (2 * (int64_t)mb * (a.rp / 64) <= dfssm::device_cu_count())
+    lora_down<2, 8, L4><<<dim3(mb, (unsigned)(a.rp / 32)), dim3(512), 0, st>>>(a);
   else
     lora_down<4, 8, L4><<<dim3(mb, (unsigned)(a.rp / 64)), dim3(512), 0, st>>>(a);
   return hipGetLastError();
