@@ -335,6 +335,12 @@ __global__ __launch_bounds__(256, 2) void mfma_tile(TileArgs a) {
   }
   const int8_t* qrd = lds + (16 * TT * wt + rho) * 128;
   const int8_t* srd = lds + D * kQStage + (16 * RT * wr + rho) * kSgRow + 4 * kg;
+  // Wide form: a wave in its K loop goes before one that writes its tile out, so
+  // the two blocks of a CU drift apart and one multiplies while the other stores
+  // (us at r = 64, without / with: 2048 x 2048 x 8512 46.3 / 44.7, 2048 x 4096 x 8512
+  // 71.5 / 69.3, 7001 x 2560 x 10576 203.9 / 202.7).  The 128 x 128 form, whose grids
+  // here fill two rounds and more, loses by it: 2048 x 4096 x 2048 35.0 / 35.5.
+  if constexpr (kX) __builtin_amdgcn_s_setprio(1);
   int slot = 0;
   for (int k = 0; k < ng; ++k) {
     // own loads of stage k landed (sign loads among the younger ones only
@@ -387,6 +393,8 @@ __global__ __launch_bounds__(256, 2) void mfma_tile(TileArgs a) {
       }
     }
   }
+
+  if constexpr (kX) __builtin_amdgcn_s_setprio(0);
 
   // ---- epilogue: the block's LoRA operands into the ring's LDS, once for all
   // waves (loads between the stores of y would each wait for their own
