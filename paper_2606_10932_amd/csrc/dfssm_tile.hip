@@ -236,7 +236,7 @@ __global__ __launch_bounds__(256, 2) void mfma_tile(TileArgs a) {
   constexpr int kSi = (kRowsS * kSgRow + 1023) / 1024;  // sign loads per group, all waves
   static_assert(kRowsQ % 32 == 0 && (G == 2 || G == 4) && D >= 2 && D <= 4 && G >= D - 1, "");
   constexpr int kLimb = 4 * kRowsQ * 64;  // the tile's limbs, then its B rows, over the ring
-  static_assert(BIG || kLimb + kRowsS * 64 <= D * kQStage + 2 * kSgBuf, "LoRA operands overlay the ring");
+  static_assert((BIG ? kRowsS * 256 : kLimb + kRowsS * 64) <= D * kQStage + 2 * kSgBuf, "LoRA operands overlay the ring");
   __shared__ __attribute__((aligned(16))) int8_t lds[D * kQStage + 2 * kSgBuf];
   __shared__ __attribute__((aligned(16))) float al_lds[kRowsS], be_lds[kRowsS], s_lds[kRowsQ];
   __shared__ __attribute__((aligned(16))) int32_t sq_lds[kRowsQ];
@@ -433,6 +433,12 @@ __global__ __launch_bounds__(256, 2) void mfma_tile(TileArgs a) {
       *reinterpret_cast<v4i*>(lds + kLimb + (idx >> 2) * 64 + 16 * ((idx & 3) ^ ((idx >> 3) & 3))) = bv[u];
     }
   }
+  if (BIG && lora) {  // B alone, all ranks: 256 bytes a row, piece p at slot p ^ (row & 15)
+    for (int idx = threadIdx.x; idx < kRowsS * (a.rp >> 4); idx += 256) {
+      const int row = idx / (a.rp >> 4), pc = idx - row * (a.rp >> 4);
+      *reinterpret_cast<v4i*>(lds + 256 * row + 16 * (pc ^ (row & 15))) = load_b(n0 + row, 16 * pc);
+    }
+  }
   __syncthreads();
   const int nl = 16 * RT * wr, ml = 16 * TT * wt;  // this wave's first row, token of the block
   if (m0 + ml >= M) return;
@@ -443,36 +449,29 @@ __global__ __launch_bounds__(256, 2) void mfma_tile(TileArgs a) {
 #pragma unroll
     for (int t = 0; t < RT; ++t) bop[t] = *reinterpret_cast<const v4i*>(lds + kLimb + (nl + 16 * t) * 64 + l_off);
   }
+  // acc_b of one 16 x 16 tile at ranks up to 64 (small: it fits 32 bits, elo
+  // alone)
+  auto up = [&](const v4i& bo, const v4i (&lm)[4], bool small, v4i& ehi, v4i& elo) {
+    ehi = elo = zero4();
+    if (!lora) return;
+    if (small) {
+      elo = mfma(bo, lm[2], elo);
+      elo = mfma(bo, lm[1], elo << 8);
+      elo = mfma(bo, lm[0], elo << 8);
+    } else {
+      ehi = mfma(bo, lm[3], ehi);
+      elo = mfma(bo, lm[1], elo);
+      ehi = mfma(bo, lm[2], ehi << 8);
+      elo = mfma(bo, lm[0], elo << 8);
+    }
+  };
   // outputs of one 16 x 16 tile: row offset rl of the run, token offset tl of
   // the block
-  auto tile_out = [&](auto is_fast, const v4i& c, const v4i& bo, const v4i (&lm)[4], bool small, int rl, int tl) {
+  auto tile_out = [&](auto is_fast, const v4i& c, const v4i& ehi, const v4i& elo, bool small, int rl, int tl) {
     constexpr bool kFast = decltype(is_fast)::value;
     const int m = m0 + tl + rho, n = n0 + rl + 4 * kg;
     const float sm = s_lds[tl + rho];
     const int nq = -sq_lds[tl + rho];
-    v4i ehi = zero4(), elo = zero4();
-    if (kFast || lora) {
-      if constexpr (BIG) {
-        v4i e[4] = {zero4(), zero4(), zero4(), zero4()};
-        for (int j0 = 0; j0 < a.rp; j0 += 64) {
-          const v4i bl = load_b(n0 + rl + rho, j0 + 16 * kg);
-#pragma unroll
-          for (int l = 0; l < 4; ++l)
-            e[l] = mfma(bl, load16(a.limbs + ((int64_t)l * M + min(m, M - 1)) * a.rp + j0 + 16 * kg), e[l]);
-        }
-        ehi = (e[3] << 8) + e[2];
-        elo = (e[1] << 8) + e[0];
-      } else if (kFast && small) {
-        elo = mfma(bo, lm[2], elo);
-        elo = mfma(bo, lm[1], elo << 8);
-        elo = mfma(bo, lm[0], elo << 8);
-      } else {
-        ehi = mfma(bo, lm[3], ehi);
-        elo = mfma(bo, lm[1], elo);
-        ehi = mfma(bo, lm[2], ehi << 8);
-        elo = mfma(bo, lm[0], elo << 8);
-      }
-    }
     const float4 al4 = *reinterpret_cast<const float4*>(&al_lds[rl + 4 * kg]);
     const float4 be4 = *reinterpret_cast<const float4*>(&be_lds[rl + 4 * kg]);
     const float alv[4] = {al4.x, al4.y, al4.z, al4.w}, bev[4] = {be4.x, be4.y, be4.z, be4.w};
@@ -521,18 +520,52 @@ __global__ __launch_bounds__(256, 2) void mfma_tile(TileArgs a) {
     for (int i = 0; i < TT; ++i) {
       const int tl = ml + 16 * i;
       if (!mine(tl)) continue;  // uniform
-      v4i lm[4];
+      if constexpr (BIG) {
+        // the limbs of one 64-rank chunk at a time, the next one on its way
+        v4i ehi[RT], elo[RT], nx[4];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) ehi[t] = elo[t] = zero4();
+        const int8_t* lp = a.limbs + (int64_t)min(m0 + tl + rho, M - 1) * a.rp + 16 * kg;
+        auto fetch = [&](int j0) {
+#pragma unroll
+          for (int l = 0; l < 4; ++l) nx[l] = load16(lp + (int64_t)l * M * a.rp + j0);
+        };
+        if (lora) fetch(0);
+        for (int j0 = 0; lora && j0 < a.rp; j0 += 64) {
+          v4i lm[4];
+#pragma unroll
+          for (int l = 0; l < 4; ++l) lm[l] = nx[l];
+          if (j0 + 64 < a.rp) fetch(j0 + 64);
+#pragma unroll
+          for (int t = 0; t < RT; ++t) {
+            const v4i bo = *reinterpret_cast<const v4i*>(lds + 256 * (nl + 16 * t + rho) + 16 * (((j0 >> 4) + kg) ^ rho));
+            ehi[t] = mfma(bo, lm[2], ehi[t] + (mfma(bo, lm[3], zero4()) << 8));
+            elo[t] = mfma(bo, lm[0], elo[t] + (mfma(bo, lm[1], zero4()) << 8));
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+          if (t < ntw) tile_out(is_fast, acc[t][i], ehi[t], elo[t], false, nl + 16 * t, tl);
+        continue;
+      }
+      v4i lm[4], ehi, elo;
       load_lm(tl, lm);
       // sum_j |acc_a| < 2^24 for every token of the tile (no limb 3, sum of
       // (|limb 2| + 1) below 256): |acc_b| < 128 * 2^24, so 32 bits hold it
       const bool small = kFast && !BIG && __all(fits32(lm));
       if (kFast && small && ntw == RT) {
 #pragma unroll
-        for (int t = 0; t < RT; ++t) tile_out(is_fast, acc[t][i], bop[t], lm, true, nl + 16 * t, tl);
+        for (int t = 0; t < RT; ++t) {
+          up(bop[t], lm, true, ehi, elo);
+          tile_out(is_fast, acc[t][i], ehi, elo, true, nl + 16 * t, tl);
+        }
       } else {
 #pragma unroll
         for (int t = 0; t < RT; ++t)
-          if (t < ntw) tile_out(is_fast, acc[t][i], bop[t], lm, false, nl + 16 * t, tl);
+          if (t < ntw) {
+            up(bop[t], lm, false, ehi, elo);
+            tile_out(is_fast, acc[t][i], ehi, elo, false, nl + 16 * t, tl);
+          }
       }
     }
     if (extra) {
@@ -543,9 +576,10 @@ __global__ __launch_bounds__(256, 2) void mfma_tile(TileArgs a) {
       for (int i = 0; i < TT / 4; ++i) {
         const int tl = 16 * (TT / 4 * wave + i);
         if (!mine(tl)) continue;
-        v4i lm[4];
+        v4i lm[4], ehi, elo;
         load_lm(tl, lm);
-        tile_out(is_fast, accx[i], bx, lm, false, kXr, tl);
+        up(bx, lm, false, ehi, elo);
+        tile_out(is_fast, accx[i], ehi, elo, false, kXr, tl);
       }
     }
   };

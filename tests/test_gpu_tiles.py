@@ -64,7 +64,9 @@ def test_split_k_tiles(env, M, K, N, r):
 @pytest.mark.parametrize("M,K,N,r", [(128, 128, 256, 64), (127, 96, 255, 16), (129, 160, 272, 17), (257, 1056, 273, 64),
                                      (140, 256, 2180, 65), (2048, 96, 8512, 8),
                                      # the down-projection's 32-rank workgroups, some past the rank; 64 again
-                                     (40, 96, 130, 17), (200, 160, 70, 97), (2049, 96, 40, 33)])
+                                     (40, 96, 130, 17), (200, 160, 70, 97), (2049, 96, 40, 33),
+                                     # ranks of three and four 64-rank chunks
+                                     (300, 128, 400, 256), (150, 160, 130, 190)])
 def test_many_token_tiles(env, form, M, K, N, r):
     torch, D, o = env
     say(f"many-token tiles form={form} {M}x{K}x{N} r{r}")
