@@ -576,13 +576,21 @@ dfssm_status dfssm_mamba2_status(const dfssm_mamba2_model* model, int64_t M, con
  *                                  every input maximum from the second
  *                                  exchange (its path for inputs with
  *                                  many near-equal largest entries)
+ *   DFSSM_TEST_LINEAR_KERNEL       1: linears of up to 16 tokens run on the
+ *                                  few-token kernel; 2..8: the split-K tile
+ *                                  kernel in form n - 2 (tokens x rows x waves
+ *                                  of a workgroup: 64x64x8, 64x64x4, 32x64x8,
+ *                                  32x64x4, 16x64x4, 16x32x8, 16x16x8) where
+ *                                  its words fit; on every path but
+ *                                  DFSSM_PATH_DECODE
  * Errors: SHAPE for an unknown switch or value. */
 typedef enum {
   DFSSM_TEST_LOCAL_LORA = 1,
   DFSSM_TEST_PREFILL_KERNEL = 2,
   DFSSM_TEST_LM_HEAD_MFMA_TOKENS = 3,
   DFSSM_TEST_STEP_PER_KERNEL = 4,
-  DFSSM_TEST_LM_HEAD_TILED_TOKENS = 5
+  DFSSM_TEST_LM_HEAD_TILED_TOKENS = 5,
+  DFSSM_TEST_LINEAR_KERNEL = 6
 } dfssm_test_switch_id;
 dfssm_status dfssm_test_switch(int which, int value);
 

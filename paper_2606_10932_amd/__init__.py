@@ -33,6 +33,7 @@ EXPORTS = ["dfssm_quantize_act", "dfssm_linear_workspace_bytes", "dfssm_scaffold
            "dfssm_version"]
 TEST_LOCAL_LORA, TEST_PREFILL_KERNEL, TEST_LM_HEAD_MFMA_TOKENS, TEST_STEP_PER_KERNEL = 1, 2, 3, 4
 TEST_LM_HEAD_TILED_TOKENS = 5
+TEST_LINEAR_KERNEL = 6
 
 
 class DfssmError(RuntimeError):

@@ -63,7 +63,7 @@ dfssm_status check_ptrs(std::initializer_list<Ptr> required, std::initializer_li
   return DFSSM_OK;
 }
 
-std::atomic<int> g_switch[6];  // dfssm_test_switch values, index = switch id
+std::atomic<int> g_switch[7];  // dfssm_test_switch values, index = switch id
 
 size_t linear_ws_bytes(int64_t M, int64_t K, int64_t r) {
   return dfssm::carve_linear_workspace(nullptr, M, K, r).bytes;
@@ -92,6 +92,9 @@ bool few_is_best(int64_t M, int64_t K, int64_t N, int64_t r) {
 // last two.
 Kernel choose(int path, int64_t M, int64_t K, int64_t N, int64_t r) {
   if (path == DFSSM_PATH_DECODE) return kPopcount;
+  const int forced = dfssm::test_switch(DFSSM_TEST_LINEAR_KERNEL);
+  if (forced == 1 && M <= dfssm::kSkinnyMaxTokens) return kFew;
+  if (forced >= 2 && dfssm::mid_takes(M, r)) return kMid;
   if (path != DFSSM_PATH_MFMA && few_is_best(M, K, N, r)) return kFew;
   if (path == DFSSM_PATH_MFMA_FEW) return kMid;
   if (path == DFSSM_PATH_MFMA && dfssm::test_switch(DFSSM_TEST_PREFILL_KERNEL) != 0) return kTile;
@@ -139,7 +142,7 @@ hipError_t launch_linear(int path, const int8_t* q, const float* s, int64_t M, i
 }  // namespace
 
 namespace dfssm {
-int test_switch(int which) { return which > 0 && which < 6 ? g_switch[which].load(std::memory_order_relaxed) : 0; }
+int test_switch(int which) { return which > 0 && which < 7 ? g_switch[which].load(std::memory_order_relaxed) : 0; }
 }  // namespace dfssm
 
 extern "C" {
@@ -153,6 +156,7 @@ dfssm_status dfssm_test_switch(int which, int value) {
     case DFSSM_TEST_LM_HEAD_MFMA_TOKENS: ok = value >= 0; break;
     case DFSSM_TEST_STEP_PER_KERNEL: ok = value >= 0 && value <= 2; break;
     case DFSSM_TEST_LM_HEAD_TILED_TOKENS: ok = value >= 0; break;
+    case DFSSM_TEST_LINEAR_KERNEL: ok = value >= 0 && value <= 8; break;
     default: break;
   }
   if (!ok) return fail(DFSSM_ERR_SHAPE, "test switch %d: value %d", which, value);

@@ -29,6 +29,8 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 //                         256 tile of the many-token path
 //   lm_head_mfma_tokens:  0 = 8; else the token count from which the LM
 //                         head runs on the matrix cores
+//   linear_kernel:        1 = the few-token kernel up to kSkinnyMaxTokens; n >=
+//                         2 = form n - 2 of the split-K tile kernel
 int test_switch(int which);
 inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 

@@ -563,6 +563,9 @@ struct MidPlan {
   double us;
 };
 MidPlan plan_mid(int64_t M, int64_t K, int64_t N, int64_t r) {
+  // test switch linear_kernel: form n - 2
+  const int forced = dfssm::test_switch(DFSSM_TEST_LINEAR_KERNEL);
+  if (forced >= 2) return {forced - 2, 0.0};
   MidPlan best{0, std::numeric_limits<double>::infinity()};
   const int cus = dfssm::device_cu_count();
   const double k = (double)K / 1024.0;

@@ -41,8 +41,8 @@ def _check(env, path, M, K, N, r, ws, q, s, rows=None):
     assert torch.equal(y, y2) and torch.equal(y, ya), "y without accumulator outputs, automatic path"
 
 
-# (M, K, N, r): each tile form of the split-K kernel (16 to 64 tokens x 16 to 64
-# rows, 4 or 8 waves) at sizes that pick it
+# (M, K, N, r): the split-K kernel at the form that its cost model picks (every
+# form by itself below)
 MID_SHAPES = [
     (3, 768, 3352, 16), (5, 1536, 768, 16), (9, 4096, 2048, 64), (16, 2048, 8512, 64),
     (17, 32, 40, 3), (20, 96, 33, 1), (31, 224, 100, 17), (47, 1152, 129, 33),
@@ -58,6 +58,65 @@ def test_split_k_tiles(env, M, K, N, r):
     ws = S.weights(K, N, r, key=(61, M, K, N, r))
     q, s = o.quantize_act(S.activations(M, K, key=(61, M, K)))
     _check(env, D.PATH_MFMA_FEW if M <= 512 else D.PATH_MFMA, M, K, N, r, ws, q, s)
+
+
+def _check_int4(env, path, M, K, N, r, key):
+    """int4 factors against the int8 linear on the unpacked values."""
+    torch, D, o = env
+    g = np.random.default_rng([key, M, K, N, r])
+    A4 = g.integers(0, 256, (r, K // 2), dtype=np.uint8)
+    B4 = g.integers(0, 256, (N, r // 2), dtype=np.uint8)
+    ws = S.weights(K, N, r, key=(key, M, K, N, r))
+    ws["A"] = o.unpack_int4(A4, r * K).reshape(r, K)
+    ws["B"] = o.unpack_int4(B4, N * r).reshape(N, r)
+    q, s = o.quantize_act(S.activations(M, K, key=(key, M, K)))
+    ref = o.linear(q, s, **ws)
+    d = dev_weights(ws)
+    y, acc_s, acc_a, acc_b = D.scaffold_lora_linear_i4(dev(q), dev(s), d["w_bits"], d["alpha"], dev(A4), dev(B4),
+                                                       d["beta"], path=path, acc=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(acc_s), ref["acc_s"]) and np.array_equal(host(acc_a), ref["acc_a"])
+    assert np.array_equal(host(acc_b), ref["acc_b"])
+    assert_y(host(y), ref, what="int4 tiles")
+
+
+# the forms of the split-K kernel (tokens x rows x waves of a workgroup); M, N
+# and K at remainders of each, fewer 128-column steps than waves, ranks of one,
+# two and five 16-rank tiles, one and three 64-rank chunks
+FORMS = ["64x64x8", "64x64x4", "32x64x8", "32x64x4", "16x64x4", "16x32x8", "16x16x8"]
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("form", range(len(FORMS)), ids=FORMS)
+@pytest.mark.parametrize("M,K,N,r", [(5, 32, 20, 2), (37, 160, 78, 18), (129, 1056, 200, 64), (50, 224, 70, 130)])
+def test_split_k_forms(env, form, bits, M, K, N, r):
+    torch, D, o = env
+    say(f"split-K form {FORMS[form]} int{bits} {M}x{K}x{N} r{r}")
+    with forced_switch(D, D.TEST_LINEAR_KERNEL, form + 2):
+        if bits == 4:
+            _check_int4(env, D.PATH_AUTO, M, K, N, r, 65)
+        else:
+            ws = S.weights(K, N, r, key=(66, M, K, N, r))
+            q, s = o.quantize_act(S.activations(M, K, key=(66, M, K)))
+            _check(env, D.PATH_AUTO, M, K, N, r, ws, q, s)
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,K,N,r", [(1, 768, 3352, 16), (2, 160, 77, 6), (1, 32, 1, 2), (2, 256, 31, 256),
+                                     (2, 4128, 50, 72), (1, 12288, 70, 32), (2, 2048, 1000, 64), (1, 2048, 8512, 64)])
+def test_few_token_kernel(env, bits, M, K, N, r):
+    """The few-token kernel by itself: one copy of the LoRA words (r <= 32) and
+    one per XCD, one and several 64-rank chunks, K below one wave's columns and
+    above all waves', sign rows of odd words, packed B rows of 3 bytes."""
+    torch, D, o = env
+    say(f"few-token kernel int{bits} {M}x{K}x{N} r{r}")
+    with forced_switch(D, D.TEST_LINEAR_KERNEL, 1):
+        if bits == 4:
+            _check_int4(env, D.PATH_AUTO, M, K, N, r, 67)
+        else:
+            ws = S.weights(K, N, r, key=(68, M, K, N, r))
+            q, s = o.quantize_act(S.activations(M, K, key=(68, M, K)))
+            _check(env, D.PATH_AUTO, M, K, N, r, ws, q, s)
 
 
 @pytest.mark.parametrize("form", [4, 8])
@@ -107,20 +166,6 @@ def test_packed_int4_tiles(env, path, M, K, N, r):
     linear on the unpacked values."""
     torch, D, o = env
     say(f"int4 tiles {path} {M}x{K}x{N} r{r}")
-    g = np.random.default_rng([64, M, K, N, r])
-    A4 = g.integers(0, 256, (r, K // 2), dtype=np.uint8)
-    B4 = g.integers(0, 256, (N, r // 2), dtype=np.uint8)
-    ws = S.weights(K, N, r, key=(64, M, K, N, r))
-    ws["A"] = o.unpack_int4(A4, r * K).reshape(r, K)
-    ws["B"] = o.unpack_int4(B4, N * r).reshape(N, r)
-    q, s = o.quantize_act(S.activations(M, K, key=(64, M, K)))
-    ref = o.linear(q, s, **ws)
-    d = dev_weights(ws)
     p = D.PATH_MFMA_FEW if path == "few" else D.PATH_MFMA
     with forced_switch(D, D.TEST_PREFILL_KERNEL, {"tile4": 4, "tile8": 8}.get(path, 0)):
-        y, acc_s, acc_a, acc_b = D.scaffold_lora_linear_i4(dev(q), dev(s), d["w_bits"], d["alpha"], dev(A4), dev(B4),
-                                                           d["beta"], path=p, acc=True)
-    torch.cuda.synchronize()
-    assert np.array_equal(host(acc_s), ref["acc_s"]) and np.array_equal(host(acc_a), ref["acc_a"])
-    assert np.array_equal(host(acc_b), ref["acc_b"])
-    assert_y(host(y), ref, what="int4 tiles")
+        _check_int4(env, p, M, K, N, r, 64)
