@@ -230,7 +230,7 @@ __device__ __forceinline__ void mid_lora(const MidArgs& a, int8_t* lds, uint32_t
 // BIG: ranks above 64 (rp > 64), a separate instantiation: its chunk loop costs
 // registers
 template <int TT, int RT, int KW, int D, bool L4, bool BIG>
-__global__ __launch_bounds__(64 * KW, TT == 1 ? 4 : 2) void mfma_mid(MidArgs a) {
+__global__ __launch_bounds__(64 * KW, TT == 1 && !BIG ? 4 : 2) void mfma_mid(MidArgs a) {
   using L = WaveLds<TT, RT, D>;
   constexpr int kTiles = TT * RT;
   constexpr int P = kTiles >= KW ? kTiles / KW : 1;  // tiles a wave finishes
@@ -460,42 +460,32 @@ __global__ __launch_bounds__(64 * KW, TT == 1 ? 4 : 2) void mfma_mid(MidArgs a) 
     }
     limb_operands(val, lm);
   };
-  finish_poll(0, true);
 
   v4i ehi[P], elo[P];
 #pragma unroll
   for (int p = 0; p < P; ++p) ehi[p] = elo[p] = zero4();
-  if (r > 0) {
-    if constexpr (!BIG) {
+  auto up = [&] {  // one 64-rank chunk
 #pragma unroll
-      for (int p = 0; p < P; ++p) {
-        ehi[p] = mfma(bop[p], lm[3], zero4());
-        elo[p] = mfma(bop[p], lm[1], zero4());
-        ehi[p] = mfma(bop[p], lm[2], ehi[p] << 8);
-        elo[p] = mfma(bop[p], lm[0], elo[p] << 8);
-      }
-    } else {
-      v4i e[P][4];
-#pragma unroll
-      for (int p = 0; p < P; ++p)
-#pragma unroll
-        for (int l = 0; l < 4; ++l) e[p][l] = mfma(bop[p], lm[l], zero4());
-      for (int c = 1; c < a.rp >> 6; ++c) {
+    for (int p = 0; p < P; ++p) {
+      ehi[p] = mfma(bop[p], lm[2], ehi[p] + (mfma(bop[p], lm[3], zero4()) << 8));
+      elo[p] = mfma(bop[p], lm[0], elo[p] + (mfma(bop[p], lm[1], zero4()) << 8));
+    }
+  };
+  if constexpr (!BIG) {
+    finish_poll(0, true);
+    if (r > 0) up();
+  } else {
+#pragma unroll 1
+    for (int c = 0; c < a.rp >> 6; ++c) {
+      if (c > 0) {
         poll(c, false);
-        finish_poll(c, false);
 #pragma unroll
-        for (int p = 0; p < P; ++p) {
-          const v4i bl = load16_row_guarded<L4>(a.B + (int64_t)min(n0 + 16 * (ft + p) + rho, N - 1) * bpitch,
-                                                64 * c + 16 * kg, r, ba);
-#pragma unroll
-          for (int l = 0; l < 4; ++l) e[p][l] = mfma(bl, lm[l], e[p][l]);
-        }
+        for (int p = 0; p < P; ++p)
+          bop[p] = load16_row_guarded<L4>(a.B + (int64_t)min(n0 + 16 * (ft + p) + rho, N - 1) * bpitch,
+                                          64 * c + 16 * kg, r, ba);
       }
-#pragma unroll
-      for (int p = 0; p < P; ++p) {
-        ehi[p] = (e[p][3] << 8) + e[p][2];
-        elo[p] = (e[p][1] << 8) + e[p][0];
-      }
+      finish_poll(c, c == 0);
+      up();
     }
   }
   if (mtok >= M) return;
@@ -580,6 +570,19 @@ MidPlan plan_mid(int64_t M, int64_t K, int64_t N, int64_t r) {
   return best;
 }
 
+template <bool L4, bool BIG>
+hipError_t launch_form(int form, const MidArgs& a, hipStream_t st) {
+  switch (form) {
+    case 0: return launch_t<4, 4, 8, 2, L4, BIG>(a, st);
+    case 1: return launch_t<4, 4, 4, 2, L4, BIG>(a, st);
+    case 2: return launch_t<2, 4, 8, 2, L4, BIG>(a, st);
+    case 3: return launch_t<2, 4, 4, 2, L4, BIG>(a, st);
+    case 4: return launch_t<1, 4, 4, 2, L4, BIG>(a, st);
+    case 5: return launch_t<1, 2, 8, 2, L4, BIG>(a, st);
+    default: return launch_t<1, 1, 8, 2, L4, BIG>(a, st);
+  }
+}
+
 template <bool L4>
 hipError_t mid_impl(const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N, int64_t r,
                     const uint32_t* w_bits, const float* alpha, const int8_t* A, const int8_t* B,
@@ -596,16 +599,8 @@ hipError_t mid_impl(const int8_t* q, const float* s, int64_t M, int64_t K, int64
   MidArgs a{q, s, (int)M, (int)K, (int)N, (int)r, rp, w_bits, alpha, A, B, beta, y, acc_s, r > 0 ? acc_a_out : nullptr,
             acc_b, ws.xw, dev ? ws.epoch : nullptr, dev ? 0u : next_host_tag(), 0, 0, 0, 0, 0,
             local_only ? 0 : (1 << 14)};
-  if (rp > 64) return launch_t<2, 4, 8, 2, L4, true>(a, st);
-  switch (plan_mid(M, K, N, r).form) {
-    case 0: return launch_t<4, 4, 8, 2, L4>(a, st);
-    case 1: return launch_t<4, 4, 4, 2, L4>(a, st);
-    case 2: return launch_t<2, 4, 8, 2, L4>(a, st);
-    case 3: return launch_t<2, 4, 4, 2, L4>(a, st);
-    case 4: return launch_t<1, 4, 4, 2, L4>(a, st);
-    case 5: return launch_t<1, 2, 8, 2, L4>(a, st);
-    default: return launch_t<1, 1, 8, 2, L4>(a, st);
-  }
+  const int form = plan_mid(M, K, N, r).form;
+  return rp > 64 ? launch_form<L4, true>(form, a, st) : launch_form<L4, false>(form, a, st);
 }
 
 }  // namespace
