@@ -67,8 +67,9 @@ inline int64_t plane_chunks(int64_t K) { return ceil_div(K, 128); }
 // (the split-K tile kernel above the former).
 constexpr int64_t kSkinnyMaxTokens = 16;
 constexpr int64_t kFewPathMaxTokens = 512;
-// Exchange words of the few-token and the split-K tile kernel: M*rp limb
-// words, then M sum-Q words (M in whole 16-token tiles), for every M <= kFewPathMaxTokens and r <= kMaxRank.
+// Exchange words of the few-token and the split-K tile kernel: a limb word per
+// token and rank, then a sum-Q word per token (tokens and ranks in whole tiles
+// of 16), for every M <= kFewPathMaxTokens and r <= kMaxRank.
 constexpr int64_t kXwWords = kFewPathMaxTokens * kMaxRank + kFewPathMaxTokens;
 // Epoch words of the few-token kernel (its arrivals spread over them) and
 // their spacing in 64-bit words.

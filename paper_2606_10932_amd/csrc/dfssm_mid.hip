@@ -51,21 +51,26 @@ struct MidArgs {
   int32_t* acc_s_out;
   int32_t* acc_a_out;
   int64_t* acc_b_out;
-  uint64_t* xw;     // limb words [token tile][rank chunk of 64][16][64 lanes], then sum-Q words [token]
+  uint64_t* xw;     // limb words [group of token tiles][rank chunk of 64][16][64 lanes], then sum-Q words [token]
   uint64_t* epoch;  // device epoch words, or NULL: the call's tag is host_tag
   uint32_t host_tag;
   int arrivals;     // workgroups per call
+  int tsh;          // 2^tsh token tiles per group: up to rank 16 (32) a tile has words for 16 (32) of the 64 lanes
   int nb_lora;      // LoRA workgroups at the front of the grid
   int nrt;          // 16-rank tiles they cover
   int ntb, nrb;     // token blocks, row blocks
   int spin;         // polls of a missing word before computing it locally
 };
 
+// The 16 words of a lane lie 512 bytes apart at every rank: 128 apart, calls of
+// few tokens took 0.2 us longer.
 __device__ __forceinline__ uint64_t* limb_words(const MidArgs& a, int tile, int chunk) {
-  return a.xw + ((int64_t)tile * (a.rp >> 6) + chunk) * 1024;
+  const int g = tile >> a.tsh, sub = tile - (g << a.tsh);
+  return a.xw + ((int64_t)g * (a.rp >> 6) + chunk) * 1024 + (sub << (6 - a.tsh));
 }
 __device__ __forceinline__ uint64_t* sumq_words(const MidArgs& a) {
-  return a.xw + (int64_t)((a.M + 15) >> 4) * 16 * a.rp;
+  const int tiles = (a.M + 15) >> 4;
+  return a.xw + (a.r > 0 ? (int64_t)((tiles + (1 << a.tsh) - 1) >> a.tsh) * 16 * a.rp : 0);
 }
 
 // ---- direct-to-LDS staging.  An MFMA operand has one row per lane, so a load
@@ -583,6 +588,8 @@ hipError_t launch_form(int form, const MidArgs& a, hipStream_t st) {
   }
 }
 
+int tile_shift(int64_t r) { return r <= 16 ? 2 : (r <= 32 ? 1 : 0); }
+
 template <bool L4>
 hipError_t mid_impl(const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N, int64_t r,
                     const uint32_t* w_bits, const float* alpha, const int8_t* A, const int8_t* B,
@@ -597,7 +604,7 @@ hipError_t mid_impl(const int8_t* q, const float* s, int64_t M, int64_t K, int64
   const bool local_only = test_switch(DFSSM_TEST_LOCAL_LORA) == 1;
   const bool dev = wants_device_epoch(st);
   MidArgs a{q, s, (int)M, (int)K, (int)N, (int)r, rp, w_bits, alpha, A, B, beta, y, acc_s, r > 0 ? acc_a_out : nullptr,
-            acc_b, ws.xw, dev ? ws.epoch : nullptr, dev ? 0u : next_host_tag(), 0, 0, 0, 0, 0,
+            acc_b, ws.xw, dev ? ws.epoch : nullptr, dev ? 0u : next_host_tag(), 0, tile_shift(r), 0, 0, 0, 0,
             local_only ? 0 : (1 << 14)};
   const int form = plan_mid(M, K, N, r).form;
   return rp > 64 ? launch_form<L4, true>(form, a, st) : launch_form<L4, false>(form, a, st);
@@ -607,7 +614,10 @@ hipError_t mid_impl(const int8_t* q, const float* s, int64_t M, int64_t K, int64
 
 namespace dfssm {
 
-bool mid_takes(int64_t M, int64_t r) { return round_up(M, 16) * (rank_padded(r) + 1) <= kXwWords; }
+bool mid_takes(int64_t M, int64_t r) {
+  const int64_t tiles = ceil_div(M, 16);
+  return (r > 0 ? ceil_div(tiles, 1 << tile_shift(r)) * 16 * rank_padded(r) : 0) + 16 * tiles <= kXwWords;
+}
 
 double mid_cost_us(int64_t M, int64_t K, int64_t N, int64_t r) { return plan_mid(M, K, N, r).us; }
 

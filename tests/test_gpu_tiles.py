@@ -101,6 +101,17 @@ def test_split_k_forms(env, form, bits, M, K, N, r):
             _check(env, D.PATH_AUTO, M, K, N, r, ws, q, s)
 
 
+@pytest.mark.parametrize("M,K,N,r", [(2500, 64, 40, 0), (7680, 32, 24, 14), (2030, 96, 33, 50)])
+def test_split_k_words_of_small_ranks(env, M, K, N, r):
+    """More tokens than the words of rank 64 leave room for."""
+    torch, D, o = env
+    say(f"split-K words {M}x{K}x{N} r{r}")
+    ws = S.weights(K, N, r, key=(69, M, K, N, r))
+    q, s = o.quantize_act(S.activations(M, K, key=(69, M, K)))
+    with forced_switch(D, D.TEST_LINEAR_KERNEL, 5):
+        _check(env, D.PATH_MFMA, M, K, N, r, ws, q, s)
+
+
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,K,N,r", [(1, 768, 3352, 16), (2, 160, 77, 6), (1, 32, 1, 2), (2, 256, 31, 256),
                                      (2, 4128, 50, 72), (1, 12288, 70, 32), (2, 2048, 1000, 64), (1, 2048, 8512, 64)])
