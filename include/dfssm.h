@@ -76,11 +76,10 @@ typedef enum { DFSSM_F16 = 0, DFSSM_F32 = 1 } dfssm_dtype;
 
 /* Kernel family selection for dfssm_scaffold_lora_linear_ex. */
 typedef enum {
-  DFSSM_PATH_AUTO = 0,     /* the few-token kernel at 1 and 2 tokens (up to
-                              16 where few rows make it the fastest), else
-                              the split-K tile kernel or the many-token
-                              path, by modelled cost (see the
-                              implementation) */
+  DFSSM_PATH_AUTO = 0,     /* the few-token kernel at 1 and 2 tokens where it
+                              is the faster one, else the split-K tile kernel
+                              or the many-token path, by modelled cost (see
+                              the implementation) */
   DFSSM_PATH_DECODE = 1,   /* bit-plane popcount GEMV (any M, best for M <= 4) */
   DFSSM_PATH_MFMA = 2,     /* sign bits expanded on chip + int8 MFMA: the
                               split-K tile kernel, or for many tokens
@@ -88,12 +87,12 @@ typedef enum {
                               of 128 tokens x 128 or 256 rows
                               (dfssm_test_switch can force one of these). */
   DFSSM_PATH_MFMA_FEW = 3  /* the same expansion and MFMA for M <= 512 in
-                              one launch: 16 output rows and up to 16
-                              tokens per workgroup (few-token kernel), or
-                              tiles of 16 to 64 of each (split-K tile
-                              kernel), K split over the waves, the LoRA
-                              down-projection in workgroups of the same
-                              grid; M > 512 gives DFSSM_ERR_UNSUPPORTED. */
+                              one launch: 16 output rows and 1 or 2 tokens
+                              per workgroup (few-token kernel), or tiles of
+                              16 to 64 of each (split-K tile kernel), K split
+                              over the waves, the LoRA down-projection in
+                              workgroups of the same grid; M > 512 gives
+                              DFSSM_ERR_UNSUPPORTED. */
 } dfssm_path;
 
 /* Per-token absmax int8 quantisation of the activations (the int8 operand
@@ -576,7 +575,7 @@ dfssm_status dfssm_mamba2_status(const dfssm_mamba2_model* model, int64_t M, con
  *                                  every input maximum from the second
  *                                  exchange (its path for inputs with
  *                                  many near-equal largest entries)
- *   DFSSM_TEST_LINEAR_KERNEL       1: linears of up to 16 tokens run on the
+ *   DFSSM_TEST_LINEAR_KERNEL       1: linears of 1 and 2 tokens run on the
  *                                  few-token kernel; 2..8: the split-K tile
  *                                  kernel in form n - 2 (tokens x rows x waves
  *                                  of a workgroup: 64x64x8, 64x64x4, 32x64x8,

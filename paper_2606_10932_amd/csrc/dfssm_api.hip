@@ -72,33 +72,45 @@ size_t linear_ws_bytes(int64_t M, int64_t K, int64_t r) {
 // The kernels of a linear.
 enum Kernel { kPopcount, kFew, kMid, kTile };
 
-// The few-token kernel where it is the fastest one (measured against the
-// split-K tile kernel at 1 to 17 tokens on eight projections, us per call): at
-// 1 and 2 tokens, where its LoRA words reach the output workgroups sooner (1.3B
-// in_proj 5.8 / 6.2 against 6.3 / 6.5, out_proj 5.7 / 5.8 against 6.4 / 6.3),
-// unless its 16-row workgroups outnumber two per CU (2.7B in_proj 7.6 against
-// 6.6) or the rank is small and the rows many (130M in_proj, r = 16: 6.6
-// against 5.7); and up to 16 tokens for few rows of at least 2048 columns (its
-// 16-byte sign loads; 2048 -> 1024: 5.3-5.7 against 5.9).
-bool few_is_best(int64_t M, int64_t K, int64_t N, int64_t r) {
-  if (M > dfssm::kSkinnyMaxTokens) return false;
-  if (N <= 1024 && K >= 2048) return true;
-  return M <= 2 && (N <= 2048 || (r > 32 && N <= 8704));
+// The few-token kernel where it is the faster one: at 1 and 2 tokens, from 2048
+// columns.  Its time against the best form of the split-K tile kernel, each call
+// of a graph on weights of its own (400 MB in turn); nt16 = row tiles of 16:
+//  - where every wave has the same number of 512-column iterations and the waves
+//    are even in number (K = 2048, 3072, 4096, 8192, ..): r = 64, one token, K =
+//    2048 -13% (512 rows) to -4% (2048) to -9% (8512), 4096 -14% (512) to -5% (3000),
+//    8192 x 2048 -8%, but 2176 x 2048 0%, x 8512 +7%, 2560 x 8000 +7%, 1792 +5 to
+//    +12%, and 4096 x 4096, more than one of its 8-wave workgroups per CU, +4%; two
+//    tokens, K = 2048 -8 to +1%, 4096 x 1024 to 3000 +3 to -3%;
+//  - at any such K where 512 rows leave the chip to a few workgroups: 2176 -7%;
+//  - without LoRA only for long rows: 4096 x 512 4.4 / 5.5 us, 2048 x 1024 +9%;
+//  - up to rank 32 its words come in one copy, polled lane by lane: 2048 columns
+//    -20% (512 rows) to -3% (10576) at one token, -4 to +7% at two, 4096 x 1024 +10%;
+//    with int4 factors 2048 x 1024 -6%, x 8512 +12%.
+bool few_is_best(int64_t M, int64_t K, int64_t N, int64_t r, bool l4) {
+  if (M > dfssm::kSkinnyMaxTokens || K < 2048) return false;
+  const int64_t nt16 = dfssm::ceil_div(N, 16), cus = dfssm::device_cu_count();
+  if (r == 0) return K >= 4 * N;
+  if (r <= 32)
+    return (K == 2048 && (4 * nt16 <= cus || (!l4 && (M == 1 || 4 * nt16 <= 3 * cus)))) || (M == 1 && 8 * nt16 <= cus);
+  if (8 * nt16 <= cus) return true;
+  const int64_t nw = std::min<int64_t>(8, K / 512);
+  if (K % (512 * nw) != 0 || nw % 2 != 0) return false;
+  return K == 2048 || ((M == 1 || 4 * nt16 <= cus) && nt16 + dfssm::rank_padded(r) / nw <= cus);
 }
 
 // Kernel of a linear on a path.  AUTO takes the few-token kernel where it is
 // best, else the cheaper of the split-K tile kernel (its words permitting) and
 // the many-token path by their modelled costs; MFMA_FEW the first two, MFMA the
 // last two.
-Kernel choose(int path, int64_t M, int64_t K, int64_t N, int64_t r) {
+Kernel choose(int path, int64_t M, int64_t K, int64_t N, int64_t r, bool l4) {
   if (path == DFSSM_PATH_DECODE) return kPopcount;
   const int forced = dfssm::test_switch(DFSSM_TEST_LINEAR_KERNEL);
   if (forced == 1 && M <= dfssm::kSkinnyMaxTokens) return kFew;
   if (forced >= 2 && dfssm::mid_takes(M, r)) return kMid;
-  if (path != DFSSM_PATH_MFMA && few_is_best(M, K, N, r)) return kFew;
+  if (path != DFSSM_PATH_MFMA && few_is_best(M, K, N, r, l4)) return kFew;
   if (path == DFSSM_PATH_MFMA_FEW) return kMid;
   if (path == DFSSM_PATH_MFMA && dfssm::test_switch(DFSSM_TEST_PREFILL_KERNEL) != 0) return kTile;
-  return dfssm::mid_takes(M, r) && dfssm::mid_cost_us(M, K, N, r) <= dfssm::tile_cost_us(M, K, N) ? kMid : kTile;
+  return dfssm::mid_takes(M, r) && dfssm::mid_cost_us(M, K, N, r) <= dfssm::tile_cost_us(M, K, N, r) ? kMid : kTile;
 }
 
 // The linear after validation, with int8 factors or (l4) packed int4 ones,
@@ -111,7 +123,7 @@ hipError_t launch_linear(int path, const int8_t* q, const float* s, int64_t M, i
   const int8_t *A8 = static_cast<const int8_t*>(A), *B8 = static_cast<const int8_t*>(B);
   const uint8_t *A4 = static_cast<const uint8_t*>(A), *B4 = static_cast<const uint8_t*>(B);
   l4 = l4 && r > 0;
-  switch (choose(path, M, K, N, r)) {
+  switch (choose(path, M, K, N, r, l4)) {
     case kFew:
       return l4 ? dfssm::launch_skinny_linear_i4(q, s, M, K, N, r, w_bits, alpha, A4, B4, beta, y, acc_s, acc_a, acc_b,
                                                  ws, hs)

@@ -65,7 +65,7 @@ inline int64_t plane_chunks(int64_t K) { return ceil_div(K, 128); }
 
 // Largest M of the few-token kernel, and of DFSSM_PATH_MFMA_FEW on request
 // (the split-K tile kernel above the former).
-constexpr int64_t kSkinnyMaxTokens = 16;
+constexpr int64_t kSkinnyMaxTokens = 2;
 constexpr int64_t kFewPathMaxTokens = 512;
 // Exchange words of the few-token and the split-K tile kernel: a limb word per
 // token and rank, then a sum-Q word per token (tokens and ranks in whole tiles
@@ -167,7 +167,7 @@ int device_cu_count();
 // Modelled durations (us) of the split-K tile kernel and of the many-token
 // path.
 double mid_cost_us(int64_t M, int64_t K, int64_t N, int64_t r);
-double tile_cost_us(int64_t M, int64_t K, int64_t N);
+double tile_cost_us(int64_t M, int64_t K, int64_t N, int64_t r);
 
 // ---------------------------------------------------------------- chain
 // The persistent chain kernel (M = 1): one launch of one workgroup per CU

@@ -532,26 +532,47 @@ hipError_t launch_t(MidArgs a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The tile forms and their modelled cost (us): with x = workgroups per CU and
-// k = K / 1024,
-//   c0 + c1 k + (c2 + c3 k) (ceil(x) - 1) + (c4 + c5 k) (x - 1)   (x > 1),
-// that is one workgroup's chain of latencies, a step for every further round
-// of the CUs and what the rounds share.  Fitted on MI355X to calls of 1 to
-// 2016 tokens on eight projections (K = 768 to 5120, N = 768 to 10576, r = 16
-// to 64); over these and the tile kernel's sizes the chosen form is on average
-// 1% slower than the fastest one.
+// The tile forms and their modelled cost (us): with x = workgroups per CU, e =
+// ceil(x) - 1, s = max(0, x - 1) and k = K / 1024,
+//   c0 + c1 k + (c2 + c3 k) e + (c4 + c5 k) s,
+// that is one workgroup's chain of latencies, a step for every further round of
+// the CUs and what the rounds share; and (c6 + c7 min(1, e)) ceil(r / 16) / 4 up to
+// rank 64, or above, with coefficients of their own, (c6 + c7 s) g for g further
+// chunks of 64 ranks.  Fitted on MI355X to calls of 1 to 4096 tokens on 19 shapes
+// (the projections of d = 768 to 2560, and K = 512 to 16384 x N = 512 to 9600), r =
+// 0 to 256, int8 and int4, each call of a graph on weights of its own (400 MB of
+// them in turn, as a decode step meets them).  The chosen form is on average 0.3%
+// slower than the fastest one up to 17 tokens and 1-2% up to 4096 (ranks above 64:
+// 0.3%, 1-4%).
 struct MidForm {
   int tt, rt;
-  double c[6];
+  double c[8], big[8];
 };
 constexpr MidForm kMidForms[] = {
-    {4, 4, {6.515, 0.950, 5.995, 0.402, -1.766, 1.199}},  // 8 waves
-    {4, 4, {7.639, 0.897, 1.473, 0.451, 1.311, 0.800}},   // 4 waves
-    {2, 4, {5.716, 0.569, 4.490, -0.047, -1.037, 0.814}}, // 8 waves
-    {2, 4, {5.821, 0.772, 0.431, 0.119, 0.876, 0.626}},   // 4 waves
-    {1, 4, {5.213, 0.664, -0.224, 0.109, 1.133, 0.318}},  // 4 waves
-    {1, 2, {5.713, 0.290, 1.011, 0.195, 0.673, 0.069}},   // 8 waves
-    {1, 1, {5.217, 0.337, 0.762, 0.088, 0.869, 0.104}},   // 8 waves
+    // 64 x 64, 8 waves; 4 waves
+    {4, 4,
+     {6.494, 1.192, 2.777, 1.211, 1.761, 0.306, 0.072, 1.777},
+     {6.254, 1.282, 9.309, -0.792, -4.856, 2.348, 1.218, 2.058}},
+    {4, 4,
+     {8.319, 1.331, 1.041, 0.290, 1.818, 1.043, -0.681, -0.522},
+     {7.243, 1.379, 0.748, 0.093, 2.359, 0.972, 1.376, 0.937}},
+    // 32 x 64, 8 waves; 4 waves
+    {2, 4,
+     {5.564, 0.721, 2.408, 0.482, 0.218, 0.507, 0.282, 1.350},
+     {5.754, 0.712, 1.226, 0.571, 4.151, -0.002, 1.169, 0.551}},
+    {2, 4,
+     {5.904, 0.994, 0.387, 0.238, 1.014, 0.456, -0.086, -0.312},
+     {5.497, 0.970, 0.564, -0.052, 1.626, 0.752, 1.246, 0.571}},
+    // 16 x 64, 4 waves; 16 x 32 and 16 x 16, 8 waves
+    {1, 4,
+     {4.788, 0.821, 0.286, 0.071, 0.559, 0.379, 0.718, -0.129},
+     {5.320, 0.744, 0.927, -0.002, 0.586, 0.292, 1.208, 0.260}},
+    {1, 2,
+     {4.691, 0.440, 0.452, 0.095, 0.733, 0.140, 0.543, 0.457},
+     {4.927, 0.447, 0.956, 0.394, 0.134, -0.003, 1.092, 0.272}},
+    {1, 1,
+     {4.207, 0.451, 0.571, 0.075, 0.656, 0.128, 0.622, -0.092},
+     {4.623, 0.429, 0.646, 0.154, 1.102, 0.115, 1.027, 0.020}},
 };
 struct MidPlan {
   int form;
@@ -567,9 +588,12 @@ MidPlan plan_mid(int64_t M, int64_t K, int64_t N, int64_t r) {
   for (int f = 0; f < (int)(sizeof(kMidForms) / sizeof(kMidForms[0])); ++f) {
     const MidForm& F = kMidForms[f];
     const int64_t tb = dfssm::ceil_div(M, 16 * F.tt);
-    const double blocks = (double)tb * (double)(dfssm::ceil_div(N, 16 * F.rt) + dfssm::ceil_div(r, 16));
+    const double blocks = (double)tb * (double)(dfssm::ceil_div(N, 16 * F.rt) + std::max<int64_t>(1, dfssm::ceil_div(r, 16)));
     const double x = blocks / cus, e = std::max(0.0, std::ceil(x) - 1.0), s = std::max(0.0, x - 1.0);
-    const double us = F.c[0] + F.c[1] * k + (F.c[2] + F.c[3] * k) * e + (F.c[4] + F.c[5] * k) * s;
+    const double* c = r <= 64 ? F.c : F.big;
+    const double rank = r <= 64 ? (c[6] + c[7] * std::min(1.0, e)) * (double)dfssm::ceil_div(r, 16) / 4.0
+                                : (c[6] + c[7] * s) * (double)(dfssm::ceil_div(r, 64) - 1);
+    const double us = c[0] + c[1] * k + (c[2] + c[3] * k) * e + (c[4] + c[5] * k) * s + rank;
     if (us < best.us) best = {f, us};
   }
   return best;

@@ -613,24 +613,28 @@ hipError_t launch_tile(TileArgs a, hipStream_t st) {
 // (a wave 64 x 64: twice the workgroups).  Modelled cost (us, both
 // launches) with x = workgroups per CU and k = K / 1024:
 //   c0 + c1 k + (c2 + c3 k) (ceil(x) - 1) + (c4 + c5 k) (x - 1) + c6 k M / 1000
-// (x > 1), fitted on MI355X to 256 to 7001 tokens on eight projections (K =
-// 768 to 5120, N = 768 to 10576, r = 16 to 64).
+// (x > 1); above rank 64, which takes the 128 x 128 form, with g = further chunks
+// of 64 ranks, coefficients of its own and g (c7 + c8 M / 1000) more.  Fitted on
+// MI355X to 24 to 4096 tokens on 16 shapes (K = 512 to 8192, N = 512 to 10576),
+// r = 0 to 256, as the split-K tile kernel's cost is.
 struct TilePlan {
   bool wide;
   double us;
 };
-TilePlan plan_tile(int64_t M, int64_t K, int64_t N) {
-  static constexpr double kC[2][7] = {{13.322, 5.315, 4.043, 1.151, 0.673, 1.667, 0.229},
-                                      {23.377, 5.780, 4.570, 2.582, 3.502, 1.199, 0.674}};
+TilePlan plan_tile(int64_t M, int64_t K, int64_t N, int64_t r) {
+  static constexpr double kC[3][9] = {{12.674, 5.758, 4.943, 0.463, 0.518, 2.364, -0.012, 0, 0},
+                                      {19.094, 7.159, 2.719, 2.327, 5.523, 1.937, 0.128, 0, 0},
+                                      {11.609, 6.155, 7.330, 0.378, 1.778, 2.368, 0.073, 2.658, 1.026}};
   const int cus = dfssm::device_cu_count();
   const int64_t tb = dfssm::ceil_div(M, 128);
-  const double k = (double)K / 1024.0;
+  const double k = (double)K / 1024.0, m = (double)M / 1000.0;
+  const double g = (double)std::max<int64_t>(0, dfssm::ceil_div(r, 64) - 1);
   TilePlan p{false, 0.0};
-  for (int f = 0; f < 2; ++f) {
+  for (int f = 0; f < (r > 64 ? 1 : 2); ++f) {
     const int64_t rb = f ? wide_runs(tb, dfssm::ceil_div(N, 16)) : dfssm::ceil_div(N, 128);
     const double x = (double)(tb * rb) / cus, e = std::max(0.0, std::ceil(x) - 1.0), s = std::max(0.0, x - 1.0);
-    const double* c = kC[f];
-    const double us = c[0] + c[1] * k + (c[2] + c[3] * k) * e + (c[4] + c[5] * k) * s + c[6] * k * (double)M / 1000.0;
+    const double* c = kC[r > 64 ? 2 : f];
+    const double us = c[0] + c[1] * k + (c[2] + c[3] * k) * e + (c[4] + c[5] * k) * s + c[6] * k * m + g * (c[7] + c[8] * m);
     if (f == 0 || us < p.us) p = {f == 1, us};
   }
   // test switch prefill_kernel: 4 the 128 x 128 form, 8 the wide one
@@ -660,7 +664,7 @@ hipError_t launch_down(const DownArgs& a, hipStream_t st) {
 
 namespace dfssm {
 
-double tile_cost_us(int64_t M, int64_t K, int64_t N) { return plan_tile(M, K, N).us; }
+double tile_cost_us(int64_t M, int64_t K, int64_t N, int64_t r) { return plan_tile(M, K, N, r).us; }
 
 int device_cu_count() {
   static std::atomic<int> cache[64];
@@ -687,7 +691,7 @@ hipError_t launch_tile_linear(const int8_t* q, const float* s, int64_t M, int64_
   TileArgs ta{q, s, (int)M, (int)K, (int)N, (int)r, rp, w_bits, alpha, ws.limbs, B, beta, ws.sumq, y, acc_s, acc_b,
               l4 ? 1 : 0, 0, 0};
   if (rp > 64) return launch_tile<4, 4, 2, 3, 4, true>(ta, st);
-  return plan_tile(M, K, N).wide ? launch_tile<8, 4, 1, 3, 2>(ta, st) : launch_tile<4, 4, 2, 3, 4>(ta, st);
+  return plan_tile(M, K, N, r).wide ? launch_tile<8, 4, 1, 3, 2>(ta, st) : launch_tile<4, 4, 2, 3, 4>(ta, st);
 }
 
 }  // namespace dfssm
