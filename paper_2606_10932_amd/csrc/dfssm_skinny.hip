@@ -1,13 +1,14 @@
-// dfssm_skinny.hip -- scaffold + LoRA linear for a few tokens (M <= 16) on
-// the gfx950 int8 matrix cores (v_mfma_i32_16x16x64_i8).
+// dfssm_skinny.hip -- scaffold + LoRA linear for one or two tokens on the gfx950
+// int8 matrix cores (v_mfma_i32_16x16x64_i8), at the sizes where it is faster than
+// the split-K tile kernel (the choice and both sides' figures stand at the
+// dispatch).
 //
-// At a few tokens the product is still a contraction the matrix cores finish
-// in a fraction of the time the sign bits take to stream.  Here a workgroup
-// owns 16 output rows and every token, and its waves split K:
-//  * each lane loads, before any arithmetic, 16*S consecutive columns of its
-//    row's sign bits (S = 4: one 8-byte load; S = 8: one 16-byte load) and
-//    the same columns of its token's codes, then runs S MFMAs per 16-token
-//    tile.  Inside one MFMA the order of the 64 contracted columns is free as
+// The product is a contraction the matrix cores finish in a fraction of the time
+// the sign bits take to stream.  Here a workgroup owns 16 output rows and every
+// token, and its waves split K:
+//  * each lane loads, before any arithmetic, 128 consecutive columns of its
+//    row's sign bits (one 16-byte load) and the same columns of its token's
+//    codes, then runs 8 MFMAs.  Inside one MFMA the order of the 64 contracted columns is free as
 //    long as both operands use the same order, so lane (row, kg) feeds
 //    columns kc(kg) + 16v .. +15 at step v and token lane (m, kg) feeds the
 //    same columns;
@@ -19,7 +20,7 @@
 //    E_lo = 256*(B.L1) + B.L0, exact int64 acc_b = E_lo + 65536*E_hi) and the
 //    fp32 epilogue; its row operands were loaded at the start.
 // One launch: the first nb_lora workgroups compute the LoRA down-projection
-// acc_a = Q A^T (one wave per rank and 4 tokens) and sum_k Q, and publish
+// acc_a = Q A^T (one wave per rank) and sum_k Q, and publish
 // them as 64-bit words {tag, value} (value: acc_a's 4 signed base-256 limbs
 // as bytes, or sum Q) with agent-scope stores; a word is valid once its tag
 // is the call's.  A call enqueued directly takes its tag from a host counter
@@ -95,10 +96,11 @@ __device__ __forceinline__ int wave_sum(int v) {
   return (int)(p[0] + p[1]);
 }
 
-// LoRA workgroup: wave w takes item b*nw + w = (token group of 4, rank j);
-// the wave of rank 0 also sums Q.  Every 16-byte load of a 4 KB column batch
+// LoRA workgroup: wave w takes rank b*nw + w for every token; the wave of rank 0
+// also sums Q.  Every 16-byte load of a 4 KB column batch
 // is issued before the first v_dot4.
-constexpr int kPrepTokens = 4;
+constexpr int kPrepTokens = 2;
+static_assert(kPrepTokens == dfssm::kSkinnyMaxTokens, "one LoRA wave per rank");
 constexpr int kPrepBatch = 4;
 template <bool L4>
 __device__ void lora_block(const SkinnyArgs& a) {
@@ -106,14 +108,13 @@ __device__ void lora_block(const SkinnyArgs& a) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = blockDim.x >> 6;
   const int M = a.M, K = a.K, r = a.r, rp = a.rp;
-  const int item = (int)blockIdx.x * nw + wave;
-  const int j = item % rp, m0 = (item / rp) * kPrepTokens;
-  if (m0 >= M) return;
+  const int j = (int)blockIdx.x * nw + wave;
+  if (j >= rp) return;
   // a publishing wave arrives once, at its start (device-epoch calls); the
   // epoch is needed only when it publishes
   uint64_t ep_old = 0;
-  if (a.epoch && lane == 0) ep_old = dfssm_dev::arrive(a.epoch, item);
-  const int mt = min(kPrepTokens, M - m0);
+  if (a.epoch && lane == 0) ep_old = dfssm_dev::arrive(a.epoch, j);
+  const int mt = min(kPrepTokens, M);
   const bool jr = j < r, qsum = j == 0;
   int acc[kPrepTokens], qs[kPrepTokens];
 #pragma unroll
@@ -135,7 +136,7 @@ __device__ void lora_block(const SkinnyArgs& a) {
           av[u] = (jr && ok) ? load_row16<false>(arow, k) : make_uint4(0, 0, 0, 0);
 #pragma unroll
         for (int m = 0; m < kPrepTokens; ++m)
-          x[m][u] = (ok && m < mt) ? *reinterpret_cast<const uint4*>(a.q + (int64_t)(m0 + m) * K + k)
+          x[m][u] = (ok && m < mt) ? *reinterpret_cast<const uint4*>(a.q + (int64_t)m * K + k)
                                    : make_uint4(0, 0, 0, 0);
       }
 #pragma unroll
@@ -174,72 +175,64 @@ __device__ void lora_block(const SkinnyArgs& a) {
   const uint32_t tag = a.epoch ? dfssm_dev::epoch_tag(old) : a.host_tag;
   if (a.xcopies == 1) {
     if (lane < mt) {
-      const int m = m0 + lane;
-      if (jr) a.acc_a[(int64_t)m * r + j] = mine;
-      word_store(a.xw + (int64_t)m * rp + j, tag, pack_limbs(mine));  // zero limbs for ranks in [r, rp)
-      if (qsum) word_store(a.xw + (int64_t)M * rp + m, tag, (uint32_t)mine_q);
+      if (jr) a.acc_a[(int64_t)lane * r + j] = mine;
+      word_store(a.xw + (int64_t)lane * rp + j, tag, pack_limbs(mine));  // zero limbs for ranks in [r, rp)
+      if (qsum) word_store(a.xw + (int64_t)M * rp + lane, tag, (uint32_t)mine_q);
     }
   } else {
-    // lane c*mt + i stores token m0 + i's words into copy c (lane i holds
+    // lane c*mt + i stores token i's words into copy c (lane i holds
     // them).  Every instruction here delays the words: this branch's
     // shuffles cost the single copy ~0.3 us a call at r = 16, and a lane
     // modulo in their place cost more.
     const int src = lane % mt;
     const int vm = __shfl(mine, src, 64), vq = __shfl(mine_q, src, 64);
-    if (lane < mt && jr) a.acc_a[(int64_t)(m0 + lane) * r + j] = mine;
+    if (lane < mt && jr) a.acc_a[(int64_t)lane * r + j] = mine;
     if (lane < mt * a.xcopies) {
-      const int cpy = lane / mt, m = m0 + (lane - cpy * mt);
+      const int cpy = lane / mt, m = lane - cpy * mt;
       uint64_t* xc = a.xw + (int64_t)cpy * a.xstride;
       word_store(xc + (int64_t)m * rp + j, tag, pack_limbs(vm));  // zero limbs for ranks in [r, rp)
       if (qsum) word_store(xc + (int64_t)M * rp + m, tag, (uint32_t)vq);
     }
   }
-  if (a.epoch && lane == 0) dfssm_dev::advance_if_last(a.epoch, item, old, a.arrivals);
+  if (a.epoch && lane == 0) dfssm_dev::advance_if_last(a.epoch, j, old, a.arrivals);
 }
 
 // The limbs of acc_a[m][j0 + 16kg .. +15] as 4 limb operands (byte e of limb
 // t = limb t of rank j0 + 16kg + e) and, when sq is given, sum Q of token m, for
-// the lane (rho, kg) of the wave that finishes the token tile starting at t0
-// (m = min(t0 + rho, M - 1)): from the LoRA workgroups' words, or computed
-// here once `spin` polls have passed.  CP: the words come in one copy per
-// XCD, and this wave polls its XCD's copy.
-//   - CP and at most NC distinct tokens in the tile (nt): the polls are
-//     token-major.  Lane L reads rank j0 + L of each token (one 512-byte
-//     load per token), lanes below nt read the sum-Q words, and the words
-//     reach their lanes through the wave's LDS tile wx [NC][kWxPitch] (sq:
-//     wq [NC]).  More tokens per round hold more loads in registers: 16
-//     took 31 more VGPRs (a wave per SIMD), and 4 gave the int4 kernel a
-//     stack frame; NC = 4 (int8 factors) or 2 (int4).
+// the lane (rho, kg) (m = min(rho, M - 1)): from the LoRA workgroups' words, or
+// computed here once `spin` polls have passed.
+//   - CP: the words come in one copy per XCD, and this wave polls its XCD's
+//     copy token by token.  Lane L reads rank j0 + L of each token (one 512-byte
+//     load per token), lanes below M read the sum-Q words, and the words reach
+//     their lanes through the wave's LDS tile wx [kPrepTokens][kWxPitch] (sq:
+//     wq [kPrepTokens]).
 //   - otherwise each lane polls its own 16 words and keeps them once in.
 constexpr int kWxPitch = 68;  // words per token row of wx (16 bytes of skew)
-constexpr int kCoalTokens = 4;
 
-// Token-major polls of n <= NC consecutive tokens from tok0 (tok0 + n <= M)
-// in the copy xc: lane L reads rank j0 + L of each, lanes below n the sum-Q
-// words (want_sq).  On success the words are in wx rows 0 .. n-1 and wq[0 ..
-// n-1]; false once `spin` polls have passed without all of them.
-template <int NC>
-__device__ bool poll_tokens(const SkinnyArgs& a, uint32_t tag, const uint64_t* xc, int tok0, int n, int j0,
-                            bool want_sq, uint32_t* wx, int* wq) {
+// Polls of all tokens in the copy xc: lane L reads rank j0 + L of each, lanes
+// below M the sum-Q words (want_sq).  On success the words are in wx rows 0 ..
+// M-1 and wq[0 .. M-1]; false once `spin` polls have passed without all of them.
+__device__ __forceinline__ bool poll_tokens(const SkinnyArgs& a, uint32_t tag, const uint64_t* xc, int j0,
+                                            bool want_sq, uint32_t* wx, int* wq) {
   const int lane = threadIdx.x & 63;
-  const int rp = a.rp;
-  const uint64_t* wp = xc + (int64_t)tok0 * rp + j0 + lane;
-  const uint64_t* sp = xc + (int64_t)a.M * rp + tok0 + min(lane, n - 1);
+  const int rp = a.rp, M = a.M;
+  const uint64_t* wp = xc + j0 + lane;
+  const uint64_t* sp = xc + (int64_t)M * rp + min(lane, M - 1);
   for (int it = 0;; ++it) {
-    uint64_t w[NC], wqv = 0;
+    uint64_t w[kPrepTokens], wqv = 0;
 #pragma unroll
-    for (int i = 0; i < NC; ++i)
-      if (i < n) w[i] = word_load(wp + (int64_t)i * rp);  // n is uniform
+    for (int i = 0; i < kPrepTokens; ++i)
+      if (i < M) w[i] = word_load(wp + (int64_t)i * rp);  // M is uniform
     if (want_sq) wqv = word_load(sp);
     bool ok = !want_sq || (uint32_t)(wqv >> 32) == tag;
 #pragma unroll
-    for (int i = 0; i < NC; ++i)
-      if (i < n) ok = ok && (uint32_t)(w[i] >> 32) == tag;
+    for (int i = 0; i < kPrepTokens; ++i)
+      if (i < M) ok = ok && (uint32_t)(w[i] >> 32) == tag;
     if (__all(ok)) {
 #pragma unroll
-      for (int i = 0; i < NC; ++i)
-        if (i < n) wx[i * kWxPitch + lane] = (uint32_t)w[i];
-      if (want_sq && lane < n) wq[lane] = (int)(uint32_t)wqv;
+      for (int i = 0; i < kPrepTokens; ++i)
+        if (i < M) wx[i * kWxPitch + lane] = (uint32_t)w[i];
+      if (want_sq && lane < M) wq[lane] = (int)(uint32_t)wqv;
       return true;
     }
     if (it >= a.spin) return false;
@@ -247,39 +240,29 @@ __device__ bool poll_tokens(const SkinnyArgs& a, uint32_t tag, const uint64_t* x
   }
 }
 
-// pre: 0 poll here; 1 the tile's words are already in wx / wq (the
-// workgroup's waves polled them together); 2 those polls gave up.
 template <bool L4, bool CP>
-__device__ void fetch_lora(const SkinnyArgs& a, uint32_t tag, int t0, int j0, int rho, int kg, uint32_t* wx,
-                           int* wq, v4i (&lm)[4], int* sq, bool store_acc, int pre) {
-  const int lane = threadIdx.x & 63;
+__device__ __forceinline__ void fetch_lora(const SkinnyArgs& a, uint32_t tag, int j0, int rho, int kg, uint32_t* wx,
+                                           int* wq, v4i (&lm)[4], int* sq, bool store_acc) {
   const int M = a.M, rp = a.rp;
-  const int nt = max(1, min(16, M - t0));  // distinct tokens of the tile (tokens past M repeat M - 1)
-  const int m = min(t0 + min(rho, nt - 1), M - 1);
-  const uint64_t* xc = CP ? a.xw + (int64_t)dfssm_px::xcc_id() * a.xstride : a.xw;
-  constexpr int NC = L4 ? 2 : kCoalTokens;
+  const int m = min(rho, M - 1);  // tokens past M repeat the last
   uint32_t val[16], vq = 0;
   bool have = false;
-  if (CP && (pre != 0 || nt <= NC)) {  // uniform
-    if (pre == 0)
-      have = poll_tokens<NC>(a, tag, xc, min(t0, M - 1), nt, j0, sq != nullptr, wx, wq);
-    else
-      have = pre == 1;
+  if constexpr (CP) {
+    have = poll_tokens(a, tag, a.xw + (int64_t)dfssm_px::xcc_id() * a.xstride, j0, sq != nullptr, wx, wq);
     if (have) {
       // the LDS writes above and these reads are the same wave's, in order
       __builtin_amdgcn_wave_barrier();
-      const int rt = min(rho, nt - 1);
 #pragma unroll
       for (int d = 0; d < 4; ++d) {
-        const uint4 u = *reinterpret_cast<const uint4*>(wx + rt * kWxPitch + 16 * kg + 4 * d);
+        const uint4 u = *reinterpret_cast<const uint4*>(wx + m * kWxPitch + 16 * kg + 4 * d);
         val[4 * d] = u.x; val[4 * d + 1] = u.y; val[4 * d + 2] = u.z; val[4 * d + 3] = u.w;
       }
-      if (sq) vq = (uint32_t)wq[rt];
+      if (sq) vq = (uint32_t)wq[m];
       __builtin_amdgcn_wave_barrier();  // wx is written again by the next chunk's call
     }
   } else {
-    const uint64_t* wp = xc + (int64_t)m * rp + j0 + 16 * kg;
-    const uint64_t* sp = xc + (int64_t)M * rp + m;
+    const uint64_t* wp = a.xw + (int64_t)m * rp + j0 + 16 * kg;
+    const uint64_t* sp = a.xw + (int64_t)M * rp + m;
     for (int it = 0;; ++it) {
       if (!have) {
         uint64_t w[16], wqv = 0;
@@ -311,31 +294,23 @@ __device__ void fetch_lora(const SkinnyArgs& a, uint32_t tag, int t0, int j0, in
     }
     if (sq) vq = (uint32_t)lane_dot<L4>(a.A, a.q, a.K, -1, m);
   }
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      uint32_t o = 0;
-#pragma unroll
-      for (int b = 0; b < 4; ++b) o |= ((val[4 * d + b] >> (8 * t)) & 0xffu) << (8 * b);
-      lm[t][d] = (int)o;
-    }
+  limb_operands(val, lm);
   if (sq) *sq = (int)vq;
 }
 
-// One tile of up to 16 tokens; S MFMA steps per lane per iteration;
-// PM: how the output waves get the LoRA words: 0 from one copy, lane by
-// lane; 1 from their XCD's copy (a.xcopies == 8), the finishing wave alone;
-// 2 from their XCD's copy, several waves together.
-// Block: 16 output rows, nw = blockDim.x / 64 waves, wave w takes
-// iterations w, w + nw, ... of 64*S columns each.
-template <int S, bool L4, int PM>
+// Block: 16 output rows, nw = blockDim.x / 64 waves, wave w takes iterations w,
+// w + nw, ... of 128 columns per lane group, 512 in all.  CP: the LoRA words come
+// in one copy per XCD (a.xcopies == 8).  The two ways to poll are separate
+// instantiations: in one kernel their union of registers cost a wave per SIMD.
+constexpr int kSteps = 8;           // MFMAs per iteration
+constexpr int kCols = 64 * kSteps;  // columns per wave iteration
+constexpr int kSignWords = kSteps / 2;
+
+template <bool L4, bool CP>
 __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
-  constexpr bool CP = PM > 0;
   __shared__ v4i red[kMaxWaves][64];
-  __shared__ __align__(16) uint32_t wx[PM == 2 ? 16 * kWxPitch : (CP ? kCoalTokens * kWxPitch : 4)];
-  __shared__ int wq[PM == 2 ? 16 : (CP ? kCoalTokens : 1)];
-  __shared__ int gok[PM == 2 ? kMaxWaves : 1];
+  __shared__ __align__(16) uint32_t wx[CP ? kPrepTokens * kWxPitch : 4];
+  __shared__ int wq[CP ? kPrepTokens : 1];
   __shared__ uint32_t tag_lds;
   if ((int)blockIdx.x < a.nb_lora) {
     lora_block<L4>(a);
@@ -346,8 +321,6 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
   const int member = a.lora_members + ((int)blockIdx.x - a.nb_lora);
   uint64_t ep_old = 0;
   if (a.epoch && threadIdx.x == 0) ep_old = dfssm_dev::arrive(a.epoch, member);
-  constexpr int KW = 64 * S;  // columns per wave iteration
-  constexpr int SW = S / 2;   // sign words per lane per iteration
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = blockDim.x >> 6;
@@ -356,11 +329,11 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
   const int n0 = 16 * ((int)blockIdx.x - a.nb_lora);
   const int nrow = min(n0 + rho, N - 1);  // sign / B row of this lane (rows past N are never stored)
   const uint32_t* wrow = a.w_bits + (int64_t)nrow * W;
-  const int nit = (K + KW - 1) / KW;
-  const bool wvec = (W % SW) == 0;
+  const int nit = (K + kCols - 1) / kCols;
+  const bool wvec = (W % kSignWords) == 0;
 
-  // ---- the row operands of the wave that finishes token tile `wave` go
-  //      out first: B bytes of ranks 0..63, row scales, token scales
+  // ---- the row operands of the wave that finishes the tile go out first: B
+  //      bytes of ranks 0..63, row scales, token scales
   const bool fin = wave == 0;
   const int mtok = rho;  // token of this lane
   const int mc = min(mtok, M - 1);
@@ -404,31 +377,26 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
   // ---- scaffold: this wave's share of K
   v4i acc = zero4();
   for (int it = wave; it < nit; it += nw) {
-    const int kc = it * KW + kg * 16 * S;  // first column of this lane (a multiple of 64)
+    const int kc = it * kCols + kg * 16 * kSteps;  // first column of this lane
     const int wd0 = kc >> 5;
-    uint32_t sw[SW];
-    if (wvec && wd0 + SW <= W) {
-      if constexpr (S == 8) {
-        const uint4 t = *reinterpret_cast<const uint4*>(wrow + wd0);
-        sw[0] = t.x; sw[1] = t.y; sw[2] = t.z; sw[3] = t.w;
-      } else {
-        const uint2 t = *reinterpret_cast<const uint2*>(wrow + wd0);
-        sw[0] = t.x; sw[1] = t.y;
-      }
+    uint32_t sw[kSignWords];
+    if (wvec && wd0 + kSignWords <= W) {
+      const uint4 t = *reinterpret_cast<const uint4*>(wrow + wd0);
+      sw[0] = t.x; sw[1] = t.y; sw[2] = t.z; sw[3] = t.w;
     } else {
       // signs past K meet zero codes; only the load has to stay in the row
 #pragma unroll
-      for (int i = 0; i < SW; ++i) sw[i] = wd0 + i < W ? wrow[wd0 + i] : 0u;
+      for (int i = 0; i < kSignWords; ++i) sw[i] = wd0 + i < W ? wrow[wd0 + i] : 0u;
     }
-    v4i x[S];
+    v4i x[kSteps];
     const int8_t* qrow = a.q + (int64_t)min(rho, M - 1) * K;
 #pragma unroll
-    for (int v = 0; v < S; ++v) {
+    for (int v = 0; v < kSteps; ++v) {
       const int col = kc + 16 * v;  // K % 32 == 0: 16 columns are wholly in or out
       x[v] = (rho < M && col < K) ? load16(qrow + col) : zero4();
     }
 #pragma unroll
-    for (int v = 0; v < S; ++v) acc = mfma(expand16_at(sw[v >> 1], 16 * (v & 1)), x[v], acc);
+    for (int v = 0; v < kSteps; ++v) acc = mfma(expand16_at(sw[v >> 1], 16 * (v & 1)), x[v], acc);
   }
 
   // ---- sum the waves' partial tiles; wave 0 finishes the tile
@@ -443,39 +411,16 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
   }
   __syncthreads();
   const uint32_t tag = tag_lds;
-  // with more tokens than one wave's polls take (G), the first ceil(n / G)
-  // waves of a one-tile workgroup each poll G tokens into the tile's LDS
-  // rows, and all meet at a barrier (one wave holding 16 tokens' loads
-  // would take 31 more VGPRs)
-  int pre = 0;
-  if constexpr (PM == 2) {
-    {
-      constexpr int G = L4 ? 2 : kCoalTokens;
-      const int ntk = min(16, M);
-      const int ng = (ntk + G - 1) / G;  // <= nw (host)
-      if (wave < ng) {
-        const uint64_t* xc = a.xw + (int64_t)dfssm_px::xcc_id() * a.xstride;
-        const int t = G * wave, n = min(G, ntk - t);
-        const bool ok = poll_tokens<G>(a, tag, xc, t, n, 0, true, wx + t * kWxPitch, wq + t);
-        if (lane == 0) gok[wave] = ok ? 1 : 0;
-      }
-      __syncthreads();
-      pre = 1;
-      for (int w = 0; w < ng; ++w)
-        if (gok[w] == 0) pre = 2;
-    }
-  }
   if (!fin) return;
   v4i d = red[0][lane];
   for (int w = 1; w < nw; ++w) d += red[w][lane];
 
-  // LoRA limbs of ranks 0..63 and sum Q of this lane's token; the first
-  // block of each tile row also keeps acc_a for the caller if its words had
-  // to be computed here
+  // LoRA limbs of ranks 0..63 and sum Q of this lane's token; the first block
+  // also keeps acc_a for the caller if its words had to be computed here
   v4i lm[4];
   int sq = 0;
   const bool keep = (int)blockIdx.x == a.nb_lora && mtok < M;
-  fetch_lora<L4, CP>(a, tag, 0, 0, rho, kg, wx, wq, lm, &sq, keep, pre);
+  fetch_lora<L4, CP>(a, tag, 0, rho, kg, wx, wq, lm, &sq, keep);
 
   // LoRA up-projection, limbs 3, 2, 1, 0 over the 64-rank chunks
   if (L4 && bpacked) {
@@ -495,7 +440,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
     for (int j0 = 64; j0 < a.rp; j0 += 64) {
       const v4i bl = load16_row_guarded<L4>(a.B + (int64_t)nrow * bpitch, j0 + 16 * kg, r, ba);
       v4i lj[4];
-      fetch_lora<L4, CP>(a, tag, 0, j0, rho, kg, wx, wq, lj, nullptr, keep, 0);
+      fetch_lora<L4, CP>(a, tag, j0, rho, kg, wx, wq, lj, nullptr, keep);
       e3 = mfma(bl, lj[3], e3);
       e2 = mfma(bl, lj[2], e2);
       e1 = mfma(bl, lj[1], e1);
@@ -529,22 +474,6 @@ __global__ __launch_bounds__(64 * kMaxWaves) void mfma_skinny(SkinnyArgs a) {
   }
 }
 
-template <bool L4, int PM>
-hipError_t launch_t(const SkinnyArgs& a, int S, int nw, hipStream_t st) {
-  const dim3 grid((unsigned)(a.nb_lora + dfssm::ceil_div(a.N, 16))), block(64 * nw);
-  if (S == 8)
-    mfma_skinny<8, L4, PM><<<grid, block, 0, st>>>(a);
-  else
-    mfma_skinny<4, L4, PM><<<grid, block, 0, st>>>(a);
-  return hipGetLastError();
-}
-
-}  // namespace
-
-namespace {
-
-using dfssm::ceil_div;
-
 template <bool L4>
 hipError_t skinny_impl(const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N, int64_t r,
                        const uint32_t* w_bits, const float* alpha, const int8_t* A, const int8_t* B,
@@ -554,47 +483,35 @@ hipError_t skinny_impl(const int8_t* q, const float* s, int64_t M, int64_t K, in
   if (M == 0 || N == 0) return hipSuccess;
   if (M > kSkinnyMaxTokens) return hipErrorInvalidValue;
   const int rp = (int)rank_padded(r);
-  // 16-byte sign loads (8 MFMA steps) once K gives 4 waves a full one each:
-  // at K = 2048 the 1.3B in_proj's 532 workgroups of 4 waves then fit the
-  // chip's slots in one round (8 waves of 8-byte loads would not)
-  const int S = K >= 2048 ? 8 : 4;
-  const int nw = (int)std::min<int64_t>(kMaxWaves, ceil_div(K, 64 * S));
+  const int nw = (int)std::min<int64_t>(kMaxWaves, ceil_div(K, kCols));
   // Test switch local_lora: no LoRA workgroups, every lane computes its LoRA
   // values itself at once (the path a lane takes when the words never
   // arrive).
   const bool local_only = test_switch(DFSSM_TEST_LOCAL_LORA) == 1;
-  const int64_t lora_waves = ceil_div(M, kPrepTokens) * rp;
-  const int nb_lora = local_only ? 0 : (int)ceil_div(lora_waves, nw);
+  const int lora_waves = local_only ? 0 : rp;
+  const int nb_lora = (int)ceil_div(lora_waves, nw);
   const int64_t out_blocks = ceil_div(N, 16);
-  const int arrivals = (int)((local_only ? 0 : lora_waves) + out_blocks);
   // the call's tag: under graph capture from the device epoch (a replay
   // moves it on), otherwise from a host counter (no arrivals at all)
   const bool device_epoch = wants_device_epoch(st);
-  // One copy of the LoRA words per XCD, each on a 256-byte boundary (no
-  // cache line holds words of two copies), when the LoRA down-projection
-  // is the longer path (r > 32) at up to kCoalTokens tokens: every output
-  // workgroup then waits on the words, and the copies took 1.2-2.3 us off
-  // a call at M = 1 to 4 (1.3B projections, r = 64; int4 at M = 3, 4, where
-  // the polls go lane by lane: 0.8 us).  At r <= 32 the words are mostly in
-  // before the first poll, and from 5 tokens the lane-by-lane polls of one
-  // copy were as fast or faster.
-  // From G + 1 to 8 tokens (G = 4, or 2 with int4 factors) and one chunk of
-  // 64 ranks, the copies are polled by ceil(M / G) waves together (1.3B,
-  // r = 64, M = 5 / 8: in_proj 8.6 -> 7.4 / 8.4 -> 8.0 us, out_proj M = 8
-  // 8.4 -> 7.7; int4 in_proj M = 4 / 8 8.6 -> 7.6 / ~10 -> 8.4).  At 16
-  // tokens they were no faster than one copy polled lane by lane.
+  // One copy of the LoRA words per XCD, each on a 256-byte boundary (no cache line
+  // holds words of two copies), when the LoRA down-projection is the longer path
+  // (r > 32): every output workgroup then waits on the words, and the copies took
+  // 1.2-2.3 us off a call (1.3B projections, r = 64).  At r <= 32 the words are
+  // mostly in before the first poll.
   const int64_t xstride = round_up(M * rp + M, 32);
-  const int64_t gsize = L4 ? 2 : kCoalTokens;
-  const bool group = rp == 64 && M > gsize && M <= 8 && ceil_div(M, gsize) <= nw;
-  const int xcopies = r > 32 && (M <= kCoalTokens || group) && 8 * xstride <= kXwWords ? 8 : 1;
-  SkinnyArgs a{q, s, (int)M, (int)K, (int)N, (int)r, rp, w_bits, alpha, A, B, beta, y, acc_s, acc_b,
-               ws.acc_a, ws.xw, xstride, xcopies, device_epoch ? ws.epoch : nullptr, device_epoch ? 0u : next_host_tag(),
-               arrivals, (int)(local_only ? 0 : lora_waves), nb_lora, local_only ? 0 : (1 << 14)};
-  // the two poll forms are separate instantiations: in one kernel their
-  // union of registers cost a wave per SIMD and spilled
-  hipError_t e = xcopies == 1 ? launch_t<L4, 0>(a, S, nw, st)
-                 : group       ? launch_t<L4, 2>(a, S, nw, st)
-                               : launch_t<L4, 1>(a, S, nw, st);
+  const int xcopies = r > 32 ? 8 : 1;
+  static_assert(8 * (kSkinnyMaxTokens * (kMaxRank + 1) + 32) <= kXwWords, "the copies fit their region");
+  const SkinnyArgs a{q, s, (int)M, (int)K, (int)N, (int)r, rp, w_bits, alpha, A, B, beta, y, acc_s, acc_b,
+                     ws.acc_a, ws.xw, xstride, xcopies, device_epoch ? ws.epoch : nullptr,
+                     device_epoch ? 0u : next_host_tag(), (int)(lora_waves + out_blocks), lora_waves, nb_lora,
+                     local_only ? 0 : (1 << 14)};
+  const dim3 grid((unsigned)(nb_lora + out_blocks)), block(64 * nw);
+  if (xcopies == 1)
+    mfma_skinny<L4, false><<<grid, block, 0, st>>>(a);
+  else
+    mfma_skinny<L4, true><<<grid, block, 0, st>>>(a);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (acc_a_out && r > 0)
     e = hipMemcpyAsync(acc_a_out, ws.acc_a, (size_t)(M * r) * 4, hipMemcpyDeviceToDevice, st);
