@@ -343,8 +343,9 @@ dfssm_status dfssm_embed_gather(const int8_t* E, const float* scale, int64_t V, 
  * streaming the table once; from 8 tokens, when d is a multiple of 64 that
  * splits into 4..8 waves of at most 8 steps of 64 (d = 256 .. 4096), one
  * pass on the matrix cores that reads the table once for all tokens; from
- * 64 tokens (and V * d, M * d < 2^31) a tiled matrix-core kernel that
- * stages both operands in LDS (dfssm_test_switch can move both thresholds).
+ * 64 tokens (from 17, or 8 when d >= 2560, for tables of about 43,000 to
+ * 57,000 rows) and V * d, M * d < 2^31, tiled matrix-core kernels that stage
+ * both operands in LDS (dfssm_test_switch can move both thresholds).
  * All choices give the same bits.
  * Limits: 0 < d <= 16384, d % 16 == 0; 0 <= V < 2^30; M >= 0 (M or V == 0
  * is a no-op).
@@ -567,8 +568,8 @@ dfssm_status dfssm_mamba2_status(const dfssm_mamba2_model* model, int64_t M, con
  *                                  cores from n tokens instead of 8
  *   DFSSM_TEST_LM_HEAD_TILED_TOKENS n > 0: on the matrix cores, the tiled
  *                                  kernels (both operands staged in LDS)
- *                                  from n tokens instead of 64 (17 where
- *                                  the table is large)
+ *                                  from n tokens instead of the thresholds
+ *                                  at dfssm_lm_head
  *   DFSSM_TEST_STEP_PER_KERNEL     1: the decode step at M = 1 runs the
  *                                  per-kernel sequence on a prepared
  *                                  workspace too; 2: the fused step takes

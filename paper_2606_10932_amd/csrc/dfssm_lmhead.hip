@@ -568,22 +568,47 @@ hipError_t launch_wide_n(const int8_t* q, const float* s, int64_t M, int64_t d, 
   return hipGetLastError();
 }
 
-// Whether lm_head_wide takes these sizes: whole 128-byte lines per row, and
-// its workgroups (one per CU) fill at least 3/4 of the rounds they need.
-// us per call in a graph on a 50,280-row table, the kernel it replaces (below
-// 64 tokens lm_head_mfma, else lm_head_tiled) against this one:
-//   tokens      32          64          128         200         256         512
-//   d = 768     14.1/13.4   12.7/14.9   16.8/17.8   26.8/23.9   30.0/27.6   49.7/49.5
-//   d = 1152    17.9/15.7   15.3/17.0   20.6/20.7   35.8/28.2   44.4/32.1   80.1/59.0
-//   d = 1536    23.5/21.5   24.0/22.5   31.2/26.3   48.8/34.0   54.0/38.0   95.3/68.5
-//   d = 2048    29.8/24.6   28.9/26.4   36.6/30.4   57.0/41.5   65.0/44.5   107.8/81.6
-//   d = 2560    41.9/31.3   37.7/33.7   46.2/38.0   71.1/48.4   78.7/51.5   130.2/96.2
-// At 200 tokens and d = 2048 its 143 MB are 3.5 TB/s; LDS reads and MFMAs of a
+// Rounds of the CUs that lm_head_wide's workgroups (one per CU) need, or 0 where
+// it is not taken: rows of whole 128-byte lines only, at least 3/4 of the rounds
+// full, and beyond 256 tokens, where token blocks read the table again, at most
+// 3/4 as many rounds as lm_head_tiled's (two workgroups of 128 x 128 per CU).  us
+// per call, tables of 600 MB in turn, lm_head_tiled / lm_head_wide:
+//   50,280 rows (1 round up to 256 tokens, 2 up to 512)
+//   tokens      65          96          128         200         256         384         512
+//   d = 768     20.0/18.4   23.2/19.3   22.1/21.9   34.6/30.2   39.0/31.8   48.6/46.7   66.6/57.4
+//   d = 1152    26.7/21.5   30.3/22.6   26.6/25.0   42.6/35.1   47.7/36.8   59.8/55.7   83.5/66.2
+//   d = 2048    40.8/29.6   45.5/30.7   37.6/33.7   58.3/45.9   64.5/47.3   78.8/74.3   110.1/88.1
+//   d = 2560    53.7/36.1   58.0/38.6   47.5/41.7   72.4/55.0   81.0/55.6   95.6/85.4   130.0/102.0
+//   114,688 rows (2 rounds) x 1024: 65 tokens 41.2/41.0, 128 49.9/49.0
+//   65,536 rows x 2048: 300 tokens (3 rounds, lm_head_tiled 3) 82.5/92.6, 512 (3, 4)
+//   127.4/118.9; 128,256 rows: 300 (5, 6) 157.2/162.0, 512 (5, 8) 241.9/208.3
+// At 200 tokens and d = 2048 its 143 MB are 3.1 TB/s; LDS reads and MFMAs of a
 // step, which only partly overlap, bound it there, the table at 64.
-bool wide_fills(int64_t M, int64_t d, int64_t V) {
-  const int64_t wgs = dfssm::ceil_div(V, kWdRows) * dfssm::ceil_div(M, 64 * kWdMaxNJ);
+int64_t wide_rounds(int64_t M, int64_t d, int64_t V) {
   const int64_t cus = dfssm::device_cu_count();
-  return d % 128 == 0 && 4 * wgs >= 3 * cus * dfssm::ceil_div(wgs, cus);
+  const int64_t ntb = dfssm::ceil_div(M, 64 * kWdMaxNJ);
+  const int64_t wgs = dfssm::ceil_div(V, kWdRows) * ntb, rounds = dfssm::ceil_div(wgs, cus);
+  const int64_t tiled = dfssm::ceil_div(dfssm::ceil_div(V, kTlRows) * dfssm::ceil_div(M, 128), 2 * cus);
+  return d % 128 == 0 && 4 * wgs >= 3 * cus * rounds && (ntb == 1 || 4 * rounds <= 3 * tiled) ? rounds : 0;
+}
+
+// Tokens from which the tiled kernels take over from lm_head_mfma, which walks the
+// tokens in series but leaves no round half full: 64, or 17 (8 from 2560 columns)
+// where lm_head_wide needs one round.  us per call as above, lm_head_mfma /
+// lm_head_wide / lm_head_tiled<64>:
+//   tokens      8               16              17              32              64
+//   50,280 rows
+//   d = 768     12.0/15.0/13.6  12.9/15.2/13.8  14.7/15.3/14.4  15.8/15.8/14.9  21.0/17.5/16.5
+//   d = 1152    16.2/17.8/17.9  17.1/17.9/18.0  19.2/17.9/18.5  20.4/18.4/19.1  26.6/20.4/20.8
+//   d = 2048    24.2/25.6/26.6  25.9/25.8/27.2  27.2/26.0/27.6  29.8/26.5/28.7  38.7/28.5/30.8
+//   d = 2560    33.9/30.5/34.8  36.1/30.8/35.5  40.4/31.0/35.9  43.0/32.0/37.1  54.9/35.0/39.3
+//   114,688 rows
+//   d = 1024    24.3/33.5/28.5  25.9/34.2/29.3  29.5/34.5/29.8  30.6/35.7/31.5  41.5/39.6/36.7
+//   d = 2048    43.7/53.1/51.1  45.6/53.8/52.6  47.2/54.1/53.7  51.5/55.2/55.9  66.7/59.9/61.2
+int64_t tiled_tokens(int64_t rounds, int64_t d) {
+  const int forced = dfssm::test_switch(DFSSM_TEST_LM_HEAD_TILED_TOKENS);
+  if (forced > 0) return forced;
+  return rounds == 1 ? (d >= 2560 ? 8 : 17) : 64;
 }
 
 // as few token blocks as 256 tokens each allow, evenly filled
@@ -679,14 +704,12 @@ hipError_t launch_lm_head(const int8_t* q, const float* s, int64_t M, int64_t d,
   // below as GEMV passes of up to 4 tokens
   const int ks = mfma_steps(d);
   if (M >= lm_head_mfma_tokens() && ks > 0) {
-    // from 64 tokens, or 17 where the table is large, a tiled kernel (the load
-    // offsets of both are 32-bit)
-    const bool fills = wide_fills(M, d, V);
-    const int forced = dfssm::test_switch(DFSSM_TEST_LM_HEAD_TILED_TOKENS);
-    if (M >= (forced > 0 ? forced : fills ? 17 : 64) && V * d < (int64_t)1 << 31 && M * d < (int64_t)1 << 31) {
-      // up to 64 tokens and below 1536 columns a stage of 14 KB of E is too
-      // short a pass for one workgroup per CU: 64-token tiles there
-      if (fills && (M > 64 || d >= 1536)) return launch_wide(q, s, M, d, E, scale, V, logits, acc, st);
+    // a tiled kernel (the load offsets of both are 32-bit); up to 64 tokens and
+    // below 1152 columns a stage of 14 KB of E is too short a pass for one
+    // workgroup per CU: 64-token tiles there
+    const int64_t rounds = wide_rounds(M, d, V);
+    if (M >= tiled_tokens(rounds, d) && V * d < (int64_t)1 << 31 && M * d < (int64_t)1 << 31) {
+      if (rounds > 0 && (M > 64 || d >= 1152)) return launch_wide(q, s, M, d, E, scale, V, logits, acc, st);
       return M >= 128 ? launch_tiled<128>(q, s, M, d, E, scale, V, logits, acc, st)
                       : launch_tiled<64>(q, s, M, d, E, scale, V, logits, acc, st);
     }

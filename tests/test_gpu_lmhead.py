@@ -223,7 +223,10 @@ def test_embed_gather_ids_outside_table(env):
     (129, 384, 43012),   # three; 3 table stages, as many as are in flight
     (200, 640, 43009),   # four, the last wave partly filled; the ring wraps
     (256, 512, 43009),   # four, all filled
-    (257, 256, 43009),   # two token blocks
+    (257, 256, 43009),   # as many rounds as the tiled kernel's: that one
+    (500, 256, 43009),   # two token blocks
+    (8, 2560, 43009),    # the fewest tokens at 2560 columns
+    (17, 1152, 43009),   # the fewest columns up to 64 tokens
     (33, 768, 43009),    # few columns: 64-token tiles
     (70, 320, 43009),    # rows that are no whole 128-byte lines: tiled kernel
 ])
