@@ -4,8 +4,8 @@
 // One workgroup of 256 threads per token row: max|x| over the row (wave64
 // butterfly, then across the 4 waves through LDS), then the codes.  Rows are
 // read with 16-byte loads when the row start and stride allow it, and held in
-// registers between the two where VPT loads per thread cover them (4: 4096
-// fp32 or 8192 fp16 columns); longer or unaligned rows are read again.
+// registers between the two where VPT loads per thread cover them (8: 8192
+// fp32 or 16384 fp16 columns); longer or unaligned rows are read again.
 #include <float.h>
 
 #include "dfssm_internal.hpp"
@@ -111,6 +111,8 @@ void launch(const T* x, int64_t M, int64_t K, int64_t ldx, int8_t* q, float* s, 
     quantize_rows<T, VEC, 2><<<grid, block, 0, st>>>(x, (int)K, ldx, q, s, scale_mode);
   else if (vpt <= 4)
     quantize_rows<T, VEC, 4><<<grid, block, 0, st>>>(x, (int)K, ldx, q, s, scale_mode);
+  else if (vpt <= 8)
+    quantize_rows<T, VEC, 8><<<grid, block, 0, st>>>(x, (int)K, ldx, q, s, scale_mode);
   else
     quantize_rows<T, VEC, 0><<<grid, block, 0, st>>>(x, (int)K, ldx, q, s, scale_mode);
 }

@@ -42,10 +42,10 @@ def test_quantize(env, dtype, M, K, ldx):
     assert np.array_equal(host(s).view(np.uint32), sr.view(np.uint32))
 
 
-# rows held in registers, 1, 2 or 4 16-byte loads per thread, and the first
+# rows held in registers, 1, 2, 4 or 8 16-byte loads per thread, and the first
 # row past each
 @pytest.mark.parametrize("dtype,K", [(dt, k) for dt, cols in ((np.float16, 2048), (np.float32, 1024))
-                                     for n in (1, 2, 4) for k in (cols * n, cols * n + 32)])
+                                     for n in (1, 2, 4, 8) for k in (cols * n, cols * n + 32)])
 def test_quantize_row_lengths(env, dtype, K):
     torch, D, o = env
     say(f"quantize rows {np.dtype(dtype)} K={K}")
