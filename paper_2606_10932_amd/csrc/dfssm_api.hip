@@ -72,42 +72,38 @@ size_t linear_ws_bytes(int64_t M, int64_t K, int64_t r) {
 // The kernels of a linear.
 enum Kernel { kPopcount, kFew, kMid, kTile };
 
-// The few-token kernel where it is the faster one: at 1 and 2 tokens, from 2048
-// columns.  Its time against the best form of the split-K tile kernel, each call
-// of a graph on weights of its own (400 MB in turn); nt16 = row tiles of 16:
-//  - where every wave has the same number of 512-column iterations and the waves
-//    are even in number (K = 2048, 3072, 4096, 8192, ..): r = 64, one token, K =
-//    2048 -13% (512 rows) to -4% (2048) to -9% (8512), 4096 -14% (512) to -5% (3000),
-//    8192 x 2048 -8%, but 2176 x 2048 0%, x 8512 +7%, 2560 x 8000 +7%, 1792 +5 to
-//    +12%, and 4096 x 4096, more than one of its 8-wave workgroups per CU, +4%; two
-//    tokens, K = 2048 -8 to +1%, 4096 x 1024 to 3000 +3 to -3%;
-//  - at any such K where 512 rows leave the chip to a few workgroups: 2176 -7%;
-//  - without LoRA only for long rows: 4096 x 512 4.4 / 5.5 us, 2048 x 1024 +9%;
-//  - up to rank 32 its words come in one copy, polled lane by lane: 2048 columns
-//    -20% (512 rows) to -3% (10576) at one token, -4 to +7% at two, 4096 x 1024 +10%;
-//    with int4 factors 2048 x 1024 -6%, x 8512 +12%.
-bool few_is_best(int64_t M, int64_t K, int64_t N, int64_t r, bool l4) {
-  if (M > dfssm::kSkinnyMaxTokens || K < 2048) return false;
+// The few-token kernel where it is the faster one, at 1 and 2 tokens.  Its time
+// against the best form of the split-K tile kernel, each call of a graph on weights
+// of its own (400 MB in turn), one token / two:
+//  - above rank 32, where its words come in a copy per XCD: r = 64, 768 x 3352 -4 /
+//    +2%, 2048 x 512 -22 / -20, x 8512 -19 / -11, 2560 x 8512 -7 / -5, 4096 x 2048 -7 /
+//    -4, x 7000 -7 / +2, 16384 x 512 -13 / -9; r = 256 -10 to -27%.  Not once its
+//    waves are more than 14 a CU: 3072 x 10576 +9 / +11, 4096 x 8512 +2 / +5.
+//  - up to rank 32, one copy polled lane by lane: r = 16, 1024 x 2048 -5 / -5%, 1536
+//    x 10576 -7 / 0, 2048 x 512 -22 / -21, x 2048 -10 / -11, x 8512 -8 / +2; from 2049
+//    columns, whose waves come later to the polls, only for few rows: 2176 x 512
+//    -20 / -18, x 2048 +2 / +10, 4096 x 512 -6 / +1, x 2048 +8 / +20; and not at 512: x
+//    512 -12 / -11, x 2048 +2 / +1, x 7000 +8 / +8.
+//  - without LoRA only for few rows: 64 x 64 -26 / -25%, 2048 x 512 -20 / -18, 1536 x 768 -9 / -7, 2048 x
+//    1024 -5 / -3, x 2048 +2 / -1, 768 x 3352 +10 / +12.
+bool few_is_best(int64_t M, int64_t K, int64_t N, int64_t r) {
+  if (M > dfssm::kSkinnyMaxTokens) return false;
   const int64_t nt16 = dfssm::ceil_div(N, 16), cus = dfssm::device_cu_count();
-  if (r == 0) return K >= 4 * N;
-  if (r <= 32)
-    return (K == 2048 && (4 * nt16 <= cus || (!l4 && (M == 1 || 4 * nt16 <= 3 * cus)))) || (M == 1 && 8 * nt16 <= cus);
-  if (8 * nt16 <= cus) return true;
-  const int64_t nw = std::min<int64_t>(8, K / 512);
-  if (K % (512 * nw) != 0 || nw % 2 != 0) return false;
-  return K == 2048 || ((M == 1 || 4 * nt16 <= cus) && nt16 + dfssm::rank_padded(r) / nw <= cus);
+  if (r == 0) return 16 * nt16 <= 3 * cus;
+  if (r <= 32) return 8 * nt16 <= cus || (K > 512 && K <= 2048 && (M == 1 || nt16 <= 2 * cus));
+  return nt16 * std::min<int64_t>(8, dfssm::ceil_div(K, 512)) <= 14 * cus;
 }
 
 // Kernel of a linear on a path.  AUTO takes the few-token kernel where it is
 // best, else the cheaper of the split-K tile kernel (its words permitting) and
 // the many-token path by their modelled costs; MFMA_FEW the first two, MFMA the
 // last two.
-Kernel choose(int path, int64_t M, int64_t K, int64_t N, int64_t r, bool l4) {
+Kernel choose(int path, int64_t M, int64_t K, int64_t N, int64_t r) {
   if (path == DFSSM_PATH_DECODE) return kPopcount;
   const int forced = dfssm::test_switch(DFSSM_TEST_LINEAR_KERNEL);
   if (forced == 1 && M <= dfssm::kSkinnyMaxTokens) return kFew;
   if (forced >= 2 && dfssm::mid_takes(M, r)) return kMid;
-  if (path != DFSSM_PATH_MFMA && few_is_best(M, K, N, r, l4)) return kFew;
+  if (path != DFSSM_PATH_MFMA && few_is_best(M, K, N, r)) return kFew;
   if (path == DFSSM_PATH_MFMA_FEW) return kMid;
   if (path == DFSSM_PATH_MFMA && dfssm::test_switch(DFSSM_TEST_PREFILL_KERNEL) != 0) return kTile;
   return dfssm::mid_takes(M, r) && dfssm::mid_cost_us(M, K, N, r) <= dfssm::tile_cost_us(M, K, N, r) ? kMid : kTile;
@@ -123,7 +119,7 @@ hipError_t launch_linear(int path, const int8_t* q, const float* s, int64_t M, i
   const int8_t *A8 = static_cast<const int8_t*>(A), *B8 = static_cast<const int8_t*>(B);
   const uint8_t *A4 = static_cast<const uint8_t*>(A), *B4 = static_cast<const uint8_t*>(B);
   l4 = l4 && r > 0;
-  switch (choose(path, M, K, N, r, l4)) {
+  switch (choose(path, M, K, N, r)) {
     case kFew:
       return l4 ? dfssm::launch_skinny_linear_i4(q, s, M, K, N, r, w_bits, alpha, A4, B4, beta, y, acc_s, acc_a, acc_b,
                                                  ws, hs)
