@@ -4,11 +4,11 @@ seeded bytes: acc_s, acc_a, acc_b bit-exact, y bit-exact against the
 oracle's fp32 order and within 1e-3 of max|y| against fp64.  Every nibble
 value -8..7 occurs (the factors are uniform random bytes).
 
-Paths: the few-token kernel reading the packed bytes directly (M <= 512,
-in 64-token blocks above 32, with and without its LoRA workgroups), and the
-prefill MFMA and popcount
-paths on factors expanded in the workspace.  Shapes: the 1.3B projections,
-ragged K and N, r not a multiple of 16 (unaligned packed B rows), r = 2, 0."""
+Paths: the few-token kernel, the split-K tiles and the many-token tiles reading
+the packed bytes directly (the first two with and without their LoRA
+workgroups), and the popcount path on factors expanded in the workspace.
+Shapes: the 1.3B projections, ragged K and N, r not a multiple of 16
+(unaligned packed B rows), r = 2, 0."""
 import numpy as np
 import pytest
 
@@ -53,10 +53,10 @@ SHAPES = [
     # (M, K, N, r)
     (1, 2048, 8512, 64),     # Mamba-2-1.3B in_proj
     (1, 4096, 2048, 64),     # Mamba-2-1.3B out_proj
-    (2, 4096, 2048, 64),     # the most tokens the copies' token-major polls take (int4)
+    (2, 4096, 2048, 64),     # the most tokens the few-token kernel takes
     (4, 4096, 2048, 64),
-    (7, 2048, 8512, 64),     # the copies polled by four waves together (2 tokens each)
-    (16, 2048, 8512, 64),    # more tokens than the waves' group polls take: one copy
+    (7, 2048, 8512, 64),
+    (16, 2048, 8512, 64),
     (17, 4096, 2048, 64),    # two token tiles
     (32, 2048, 300, 64),
     (3, 160, 77, 6),         # r % 16 != 0: packed B rows of 3 bytes
@@ -65,8 +65,8 @@ SHAPES = [
     (2, 256, 40, 256),       # four 64-rank chunks
     (1, 768, 3352, 16),      # Mamba-2-130M in_proj
     (3, 64, 9, 0),
-    (70, 2048, 300, 64),     # two 64-token blocks, the second ragged
-    (200, 4096, 2048, 64),   # four blocks, out_proj shape
+    (70, 2048, 300, 64),
+    (200, 4096, 2048, 64),   # out_proj shape
 ]
 
 

@@ -126,7 +126,7 @@ def test_decode_step_against_oracle(env, model_host, M):
 
 @pytest.mark.parametrize("M,steps", [(2, 4), (130, 1)])
 def test_decode_step_int4_lora(env, model_host_i4, M, steps):
-    # int4 factors in every projection: the few-token kernel reads them
+    # int4 factors in every projection: the linears read them
     # packed (both projections at M = 2, out_proj at M = 130); in_proj at
     # M = 130 takes the prefill path on factors expanded in the workspace
     torch, D, o = env

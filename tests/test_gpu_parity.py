@@ -177,18 +177,18 @@ def test_linear_int8_min(env, path, M, K, N, r):
     assert_y(host(y), ref, what=f"int8 min {path} {M}x{K}x{N} r{r}")
 
 
-# few-token MFMA path (M <= 512; up to 32 tokens 1 or 2 token tiles per
-# workgroup, above 32 blocks of 64 tokens, 4 tiles): 8- and 16-byte sign loads, K splits of one or more iterations per
-# wave, unaligned sign rows, ragged N, rank 0, rank not a multiple of 16 and
-# ranks above 64, several chunks with a ragged last one
+# few-token MFMA path (M <= 512): the few-token kernel at 1 and 2 tokens, the
+# split-K tiles above; unaligned sign rows, ragged N, rank 0, rank not a multiple of
+# 16 and ranks above 64, K of one step and of more than every wave has, token tiles
+# filled and not
 FSHAPES = [
-    (1, 768, 3352, 16),      # Mamba-2-130M in_proj: 3 waves
+    (1, 768, 3352, 16),      # Mamba-2-130M in_proj: 2 waves of the few-token kernel
     (1, 2048, 8512, 64),     # Mamba-2-1.3B in_proj
-    (4, 2048, 8512, 64),     # the most tokens the copies' token-major polls take (int8)
+    (4, 2048, 8512, 64),
     (5, 4096, 2048, 64),     # Mamba-2-1.3B out_proj, small batches
-    (7, 2048, 8512, 64),     # the copies polled by two waves together, the second with 3 tokens
+    (7, 2048, 8512, 64),
     (8, 2048, 8512, 64),
-    (13, 2048, 8512, 64),    # above 8 tokens: one copy again
+    (13, 2048, 8512, 64),
     (16, 4096, 2048, 64),
     (17, 4096, 2048, 64),
     (32, 4096, 2048, 64),
@@ -196,15 +196,15 @@ FSHAPES = [
     (1, 32, 1, 0),
     (9, 96, 33, 1),
     (2, 256, 31, 256),       # four 64-rank chunks
-    (20, 8192, 130, 64),     # two iterations per wave
-    (32, 4128, 50, 72),      # K % 512 != 0 with 16-byte sign loads, odd row length
+    (20, 8192, 130, 64),     # 8 steps of 128 columns per wave
+    (32, 4128, 50, 72),      # K % 128 != 0, odd row length
     (12, 12288, 70, 32),
     (31, 2048, 300, 64),
-    (33, 2048, 8512, 64),    # one 64-token block holding 33 tokens
-    (65, 4096, 2048, 64),    # two blocks, the second of one token
-    (96, 4096, 2048, 64),    # two blocks, the second of two full tiles
-    (100, 160, 77, 5),       # ragged last block, odd shapes
-    (130, 4096, 2048, 64),   # three blocks, out_proj shape
+    (33, 2048, 8512, 64),    # one token past two tiles of 16
+    (65, 4096, 2048, 64),    # one past four
+    (96, 4096, 2048, 64),
+    (100, 160, 77, 5),       # ragged last tile, odd shapes
+    (130, 4096, 2048, 64),
     (200, 256, 31, 256),
     (512, 96, 33, 1),        # the largest M the path takes
 ]
@@ -227,8 +227,9 @@ def test_linear_few_tokens(env, M, K, N, r):
 @pytest.mark.parametrize("M,K,N,r", [(3, 160, 77, 5), (17, 4096, 2048, 64), (2, 256, 31, 256), (1, 32, 1, 0),
                                      (70, 2048, 300, 64)])
 def test_few_tokens_local_lora(env, M, K, N, r):
-    """The few-token kernel's fallback: with no LoRA workgroups launched and
-    no polling (a test switch of the library), every lane computes acc_a and
+    """The fallback of the few-token and the split-K tile kernel: with no LoRA
+    workgroups launched and no polling (a test switch of the library), every
+    lane computes acc_a and
     sum Q itself; the results are the same integers."""
     torch, D, o = env
     say(f"few tokens, local LoRA values M={M} K={K} N={N} r={r}")
@@ -272,21 +273,20 @@ def test_realistic_lora_ratio(env, path):
     assert_y(y, ref, what="realistic ratio")
 
 
-# the two prefill kernels (4-wave blocks, two per CU; 8-wave ping-pong
-# blocks, one per CU) on shapes the automatic choice would not give them
+# the two forms of the many-token tiles (128 tokens x 128 rows; x up to 17 row
+# tiles) on shapes the automatic choice would not give them
 PSHAPES = [
     (5, 160, 77, 5),         # K % 128 != 0, r % 4 != 0
     (33, 128, 130, 64),
     (130, 2048, 300, 64),
     (16, 4096, 2048, 64),
     (2, 256, 31, 256),       # ranks above 64: LoRA operands from memory
-    (300, 2080, 700, 64),    # K % 64 == 32: half last stage
-    (129, 96, 600, 0),       # no LoRA, 2-stage K
-    # 9 slices: runs of 4-5 row tiles take the 8-row short form, runs of 8-9
-    # the full form (smaller shapes take the 4-row short form)
-    (1100, 288, 4201, 64),   # short, 8-row form; K % 64 == 32, ragged N
+    (300, 2080, 700, 64),    # K % 128 == 32: a quarter of a last stage
+    (129, 96, 600, 0),       # no LoRA, one stage
+    # 9 token blocks
+    (1100, 288, 4201, 64),   # K % 128 == 32, ragged N
     (1030, 256, 4200, 0),
-    (1100, 288, 7400, 64),   # full form
+    (1100, 288, 7400, 64),
     (1030, 256, 7300, 0),
 ]
 
@@ -307,20 +307,18 @@ def test_linear_prefill_kernels(env, kernel, M, K, N, r):
     assert np.array_equal(y2.view(np.uint32), y.view(np.uint32)), "y without accumulator outputs"
 
 
-# the 4-wave kernel's short forms (every run of the grid at most 4, or at
-# most 8, row tiles: wave w multiplies token tiles 2w, 2w+1 of each row
-# tile and skips tiles past M), as the prefill path takes them at a few
-# hundred tokens
+# the 128 x 128 tiles at a few hundred tokens, where the last token block is partly
+# filled and blocks are few, and the automatic path's choice there
 SHORT_SHAPES = [
-    (100, 2048, 8512, 64),   # 1.3B in_proj, one partial 128-token slice
+    (100, 2048, 8512, 64),   # 1.3B in_proj, one partial token block
     (33, 768, 3352, 16),     # 130M in_proj, 3 token tiles
-    (500, 1536, 768, 64),    # 130M out_proj, 4 slices, the last partial
+    (500, 1536, 768, 64),    # 130M out_proj, 4 blocks, the last partial
     (200, 4096, 2048, 72),   # ranks above 64: LoRA operands from memory
-    (77, 2080, 210, 0),      # no LoRA, K % 64 == 32, ragged N
-    (260, 4096, 2048, 64),   # 1.3B out_proj, 3 slices
-    (300, 256, 10900, 64),   # runs of 3-4 row tiles, ragged N
-    (512, 2048, 8512, 64),   # 1.3B in_proj, runs of 4-5: the 8-row form
-    (1100, 256, 4200, 72),   # the 8-row form, ranks above 64
+    (77, 2080, 210, 0),      # no LoRA, K % 128 == 32, ragged N
+    (260, 4096, 2048, 64),   # 1.3B out_proj, 3 token blocks
+    (300, 256, 10900, 64),   # many row blocks, ragged N
+    (512, 2048, 8512, 64),   # 1.3B in_proj
+    (1100, 256, 4200, 72),   # ranks above 64
 ]
 
 
@@ -337,7 +335,7 @@ def test_linear_prefill_short_form(env, M, K, N, r):
     assert np.array_equal(acc_b, ref["acc_b"]), "acc_b"
     assert_y(y, ref, what=f"short {M}x{K}x{N} r{r}")
     assert np.array_equal(y2.view(np.uint32), y.view(np.uint32)), "y without accumulator outputs"
-    # the automatic path at this size (few-token or prefill, by the cost model)
+    # the automatic path at this size (split-K tiles or these, by the cost model)
     ya = _run_y_only(env, M, K, N, r, D.PATH_AUTO)
     assert np.array_equal(ya.view(np.uint32), y.view(np.uint32)), "automatic path"
 
@@ -345,7 +343,7 @@ def test_linear_prefill_short_form(env, M, K, N, r):
 @pytest.mark.parametrize("kernel", [0, 4])
 def test_prefill_full_size(env, kernel):
     """Mamba-2-1.3B in_proj at 2048 tokens (the launch the benchmark times,
-    which takes the 8-wave kernel; and the 4-wave kernel on the same shape):
+    which takes the wide tiles; and the 128 x 128 ones on the same shape):
     every acc_s/acc_a/acc_b and y of all 2048 token rows against the oracle."""
     torch, D, o = env
     M, K, N, r = 2048, 2048, 8512, 64

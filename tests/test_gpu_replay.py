@@ -3,9 +3,9 @@ hipGraph, then replayed with new activation codes written into its input
 buffers between replays.  Every replay must equal the oracle run on that
 replay's inputs, bit for bit.
 
-This is what the few-token kernel's device-side epoch is for: its LoRA
-workgroups publish acc_a as tagged words, and a replay whose output
-workgroups accepted a word left by the previous replay (same shape, same
+This is what the device-side epoch of the few-token and the split-K tile
+kernel is for: their LoRA workgroups publish acc_a as tagged words, and a
+replay whose output workgroups accepted a word left by the previous replay (same shape, same
 workspace, same captured arguments) would compute y from the previous
 replay's acc_a.  A new q per replay makes any such stale acceptance show in
 y (acc_a enters y through the LoRA term, about 850 times the scaffold term
@@ -15,7 +15,7 @@ import pytest
 
 import dfssm_synth as S
 import oracle
-from gpu_util import assert_y, dev, dev_weights, host, say, torch_cuda
+from gpu_util import assert_y, dev, dev_weights, forced_switch, host, say, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -66,8 +66,34 @@ def test_linear_graph_replays(env, K, N, M):
         assert_y(host(y_buf), ref, what=f"replay {t}")
 
 
+@pytest.mark.parametrize("kernel,M,r", [(1, 2, 16), (1, 1, 130), (4, 40, 20), (8, 9, 100)])
+def test_linear_graph_replays_forms(env, kernel, M, r):
+    """The few-token kernel with one copy of its words and with chunks of 64 ranks,
+    the split-K tiles with two token tiles to a group of words and with chunks."""
+    torch, D, o = env
+    K, N = 2080, 300
+    say(f"graph replay: linear kernel={kernel} M={M} K={K} N={N} r={r}")
+    ws = S.weights(K, N, r, key=(178, r))
+    d = dev_weights(ws)
+    q_buf = torch.zeros((M, K), dtype=torch.int8, device="cuda")
+    s_buf = torch.zeros((M,), dtype=torch.float32, device="cuda")
+    y_buf = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    wsp = D.linear_workspace(M, K, N, r)
+    with forced_switch(D, D.TEST_LINEAR_KERNEL, kernel):
+        g = _capture(torch, lambda: D.scaffold_lora_linear(q_buf, s_buf, d["w_bits"], d["alpha"], d["A"], d["B"],
+                                                            d["beta"], y=y_buf, workspace=wsp))
+    for t in range(REPLAYS):
+        q, s = o.quantize_act(S.activations(M, K, key=(179, M, t)))
+        q_buf.copy_(dev(q))
+        s_buf.copy_(dev(s))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert_y(host(y_buf), o.linear(q, s, **ws), what=f"replay {t}")
+
+
 def test_linear_graph_replays_eager_between(env):
-    """Replays of a captured few-token call interleaved with eager calls of
+    """Replays of a captured call interleaved with eager calls of
     another shape on the same workspace: each result from its own inputs."""
     torch, D, o = env
     M, K, N, r = 3, 4096, 2048, 64
