@@ -126,9 +126,8 @@ def test_decode_step_against_oracle(env, model_host, M):
 
 @pytest.mark.parametrize("M,steps", [(2, 4), (130, 1)])
 def test_decode_step_int4_lora(env, model_host_i4, M, steps):
-    # int4 factors in every projection: the linears read them
-    # packed (both projections at M = 2, out_proj at M = 130); in_proj at
-    # M = 130 takes the prefill path on factors expanded in the workspace
+    # int4 factors in every projection, read packed: the few-token kernel or
+    # the split-K tiles at M = 2, the tiles at M = 130
     torch, D, o = env
     say(f"decode step, int4 LoRA, M={M} vs oracle")
     m = device_model(D, model_host_i4)
