@@ -19,7 +19,7 @@
 // lines of Q (stages of 128 columns): a CU draws 57-61 bytes per clock from its
 // L2 that way and 26-41 with 64-byte pieces of rows.  Signs come in groups of
 // G stages, 16 G bytes of each row.  16-byte pieces of a row are stored
-// swizzled, so the 16 lanes of an operand read hit all banks.
+// swizzled (swz8).
 #include <algorithm>
 #include <atomic>
 #include <cmath>
