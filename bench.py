@@ -324,11 +324,14 @@ def main():
                    "frac_i8_peak": round(ops / (pms * 1e-3) / 1e12 / PEAK_I8_TOPS, 4)}
 
     # ---- single linears at decode sizes ---------------------------------------
-    # Per call: q, s -> y on the automatic path (the one-launch few-token
-    # MFMA kernel at these sizes).  The calls of one graph replay walk
+    # Per call: q, s -> y on the automatic path (one launch: the few-token
+    # kernel at one token, split-K tiles above).  The calls of one graph replay walk
     # over distinct copies of the weights, about 600 MB in all, so every call
     # meets its weights outside the 256 MB Infinity Cache; the graph removes
     # the host's launch cost from the measurement.
+    def linear_path(m):
+        return "few-token MFMA (one launch)" if m == 1 else "split-K MFMA tiles (one launch)"
+
     def read_floors(nbytes, ncall):
         """The floor under a single linear of nbytes of weights: one launch
         reading nbytes (dfssm_read_floor), over ncall distinct buffers so
@@ -427,15 +430,15 @@ def main():
                 fig = {"workload": f"{name} M={m}", "us_per_call": round(us, 2),
                        "us_per_call_warm": round(us_warm, 2),
                        "weight_gbs": round(wb / (us * 1e-6) / 1e9, 1), "weight_bytes": wb,
-                       "path": "few-token MFMA (one launch)", "lora": "int8"}
+                       "path": linear_path(m), "lora": "int8"}
                 if m == 1 and cfg > 0:
                     # the floor: a cold one-launch read of the same bytes
                     fig.update(read_floors(wb, ncall))
                 decode.append(fig)
                 del g
             del cps, base
-        # the same projections with int4 LoRA factors (packed bytes read by
-        # the few-token kernel), same method
+        # the same projections with int4 LoRA factors (the kernels read
+        # the packed bytes), same method
         for cfg, name, Ms in ((1, "Mamba-2-1.3B in_proj K=2048 N=8512 r=64", (1,)),
                               (2, "Mamba-2-1.3B out_proj K=4096 N=2048 r=64", (1, 32))):
             c = S.CONFIGS[cfg]
@@ -474,7 +477,7 @@ def main():
                 us = t0.elapsed_time(t1) * 1e3 / (reps * ncall)
                 decode.append({"workload": f"{name} M={m}", "us_per_call": round(us, 2),
                                "weight_gbs": round(wb / (us * 1e-6) / 1e9, 1), "weight_bytes": wb,
-                               "path": "few-token MFMA (one launch)", "lora": "int4"})
+                               "path": linear_path(m), "lora": "int4"})
                 del g
             del cps, base
 
