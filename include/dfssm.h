@@ -115,7 +115,7 @@ size_t dfssm_linear_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t r);
 /* The scaffold + LoRA linear (Eq. 3 with a binary scaffold), on already
  * quantised activations (q, s).  Writes y [M,N].  `workspace` is device
  * memory of at least dfssm_linear_workspace_bytes(M,K,N,r) bytes, used for
- * acc_a, per-token staging and the exchange words of the few-token path.
+ * acc_a, per-token staging and the exchange words of the one-launch kernels.
  * The workspace must hold zeros before its first use (hipMemset, or a
  * zero-filled tensor); after that it belongs to the library: pass it back
  * unchanged to later calls, of any shape and path, and do not run two

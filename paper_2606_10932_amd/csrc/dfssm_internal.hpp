@@ -22,9 +22,9 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Test switches (dfssm_test_switch), all 0 unless a test sets them: the
 // kernel-family choices below read them on the host at each launch.
-//   local_lora:           1 = the few-token kernel launches no LoRA
-//                         workgroups (every output workgroup computes those
-//                         values itself)
+//   local_lora:           1 = the few-token and split-K tile kernels launch no
+//                         LoRA workgroups (every output workgroup computes
+//                         those values itself)
 //   prefill_kernel:       0 = automatic, 4 or 8 = the 128 x 128 or the 128 x
 //                         256 tile of the many-token path
 //   lm_head_mfma_tokens:  0 = 8; else the token count from which the LM
@@ -36,8 +36,9 @@ inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
 // Per-call workspace (device), every region 256-byte aligned:
 //   epoch  uint64 [64][16]        64 words {epoch:32, arrivals:32} of the
-//                                 few-token kernel, one per 128-byte line
-//   xw     uint64 [kXwWords]      {tag, value} words of the few-token kernel:
+//                                 few-token and the split-K tile kernel, one
+//                                 per 128-byte line
+//   xw     uint64 [kXwWords]      {tag, value} words of the same two kernels:
 //                                 acc_a limbs per (token, rank), then sum Q;
 //                                 a region of fixed size at a fixed offset,
 //                                 so no other kernel or shape writes over it
@@ -71,7 +72,7 @@ constexpr int64_t kFewPathMaxTokens = 512;
 // token and rank, then a sum-Q word per token (tokens and ranks in whole tiles
 // of 16), for every M <= kFewPathMaxTokens and r <= kMaxRank.
 constexpr int64_t kXwWords = kFewPathMaxTokens * kMaxRank + kFewPathMaxTokens;
-// Epoch words of the few-token kernel (its arrivals spread over them) and
+// Epoch words of the same two kernels (their arrivals spread over them) and
 // their spacing in 64-bit words.
 constexpr int kEpochGroups = 64;
 constexpr int kEpochStride = 16;
@@ -120,9 +121,9 @@ hipError_t launch_decode_linear(const int8_t* q, const float* s, int64_t M, int6
                                 const LinearWorkspace& ws, hipStream_t st);
 
 // Few tokens (M <= kSkinnyMaxTokens) on the matrix cores, one launch: LoRA
-// workgroups publish acc_a and sum Q as tagged words while the others run a
-// split-K expanded-sign int8 MFMA product over 16 output rows each, then the
-// LoRA up-projection and epilogue.
+// workgroups publish acc_a and sum Q as tagged words while the others run an
+// expanded-sign int8 MFMA product over 16 output rows each, K split over their
+// waves, then the LoRA up-projection and epilogue.
 hipError_t launch_skinny_linear(const int8_t* q, const float* s, int64_t M, int64_t K, int64_t N,
                                 int64_t r, const uint32_t* w_bits, const float* alpha,
                                 const int8_t* A, const int8_t* B, const float* beta, float* y,

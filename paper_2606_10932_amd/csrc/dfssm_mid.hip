@@ -22,11 +22,11 @@
 //    integers itself, so no workgroup depends on another being scheduled.
 //  * Up-projection and epilogue as in the few-token kernel: four limb MFMAs
 //    per tile, exact int64 acc_b, the pinned fp32 order.
-// Measured (us per call in a graph of calls, before -> now; before: the
-// few-token kernel in 64-token blocks or the former prefill path, whichever
-// was faster): 1.3B in_proj at 9 / 45 / 128 / 301 tokens 9.1 / 20.3 / 22.8 / 27.9
-// -> 6.4 / 7.4 / 11.7 / 19.0, out_proj at 9 / 64 / 301 / 1000 8.0 / 14.1 / 32.0 /
-// 40.5 -> 6.4 / 7.4 / 10.9 / 22.4, 130M out_proj at 1000 17.6 -> 8.4.
+// Measured (us per call in a graph of calls, each on weights of its own, r = 64,
+// before -> now; before: the few-token kernel in 64-token blocks or the former
+// prefill path, whichever was faster): 1.3B in_proj at 9 / 48 / 128 / 301 tokens 9.4
+// / 20.9 / 24.4 / 28.0 -> 7.1 / 8.4 / 11.8 / 19.5, out_proj at 9 / 64 / 301 / 1000 8.0
+// / 14.5 / 33.2 / 40.6 -> 6.7 / 7.8 / 11.2 / 21.9, 130M out_proj at 1000 18.4 -> 9.3.
 #include <algorithm>
 #include <cmath>
 #include <limits>
@@ -75,11 +75,10 @@ __device__ __forceinline__ uint64_t* sumq_words(const MidArgs& a) {
 
 // ---- direct-to-LDS staging.  An MFMA operand has one row per lane, so a load
 // straight into operand registers touches 64 cache lines with every
-// instruction, and a CU drew ~10 bytes per clock that way.  So each wave
-// brings its own share of K through LDS in steps of 128 columns: lane i of a
-// 16-byte load fetches piece i % 8 of row i / 8, whole 128-byte lines (57-61
-// bytes per clock per CU measured, against 26-41 with 64-byte pieces of
-// rows).  The areas are private to the wave: no barrier, only the wave's own
+// instruction, and a CU draws 16 bytes per clock from its L2 that way.  So each
+// wave brings its own share of K through LDS in steps of 128 columns: lane i of a
+// 16-byte load fetches piece i % 8 of row i / 8, whole 128-byte lines (60 bytes
+// per clock per CU measured, against 36 with 64-byte pieces of rows).  The areas are private to the wave: no barrier, only the wave's own
 // load counter.
 // LDS of one wave: a ring of D steps of 16*TT token rows x 128 bytes, then two
 // sign buffers of 16*RT rows x 32 bytes (2 steps).  The partial tiles overlay

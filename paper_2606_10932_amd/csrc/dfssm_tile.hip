@@ -16,8 +16,8 @@
 // and the int64 -> fp32 conversion falls away.
 //
 // Operands of both kernels reach LDS by direct-to-LDS loads of whole 128-byte
-// lines of Q (stages of 128 columns): a CU draws 57-61 bytes per clock from its
-// L2 that way and 26-41 with 64-byte pieces of rows.  Signs come in groups of
+// lines of Q (stages of 128 columns): a CU draws 60 bytes per clock from its
+// L2 that way and 36 with 64-byte pieces of rows.  Signs come in groups of
 // G stages, 16 G bytes of each row.  16-byte pieces of a row are stored
 // swizzled (swz8).
 #include <algorithm>
