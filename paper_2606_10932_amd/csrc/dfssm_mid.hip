@@ -531,47 +531,53 @@ hipError_t launch_t(MidArgs a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The tile forms and their modelled cost (us): with x = workgroups per CU, e =
-// ceil(x) - 1, s = max(0, x - 1) and k = K / 1024,
-//   c0 + c1 k + (c2 + c3 k) e + (c4 + c5 k) s,
-// that is one workgroup's chain of latencies, a step for every further round of
-// the CUs and what the rounds share; and (c6 + c7 min(1, e)) ceil(r / 16) / 4 up to
-// rank 64, or above, with coefficients of their own, (c6 + c7 s) g for g further
-// chunks of 64 ranks.  Fitted on MI355X to calls of 1 to 4096 tokens on 19 shapes
-// (the projections of d = 768 to 2560, and K = 512 to 16384 x N = 512 to 9600), r =
-// 0 to 256, int8 and int4, each call of a graph on weights of its own (400 MB of
-// them in turn, as a decode step meets them).  The chosen form is on average 0.3%
-// slower than the fastest one up to 17 tokens and 1-2% up to 4096 (ranks above 64:
-// 0.3%, 1-4%).
+// The tile forms and their modelled cost (us): with x = workgroups per CU, R = the
+// workgroups that fit a CU at once (LDS and registers), e = ceil(x) - 1, s = max(0,
+// x - 1), E = ceil(x / R) - 1, m = min(1, x) and k = K / 1024,
+//   c0 + c1 k + (c2 + c3 k) e + (c4 + c5 k) s + (c6 + c7 k) E + (c8 + c9 k) m,
+// that is one workgroup's chain of latencies, what further workgroups on a CU add,
+// what they share, a step for every further round and how full the first is; c12 x
+// where N % 16 != 0 (a token's outputs then start off the 64-byte segments of a
+// tile's stores); and (c10 + c11 min(1, e)) ceil(r / 16) / 4 up to rank 64, or above,
+// with coefficients of their own, (c10 + c11 s) g for g further chunks of 64 ranks.
+// Fitted on MI355X, each call of a graph on weights of its own (400 MB of them in
+// turn, as a decode step meets them): a grid of 3 to 4096 tokens on 19 shapes (K =
+// 512 to 16384 x N = 512 to 9600), r = 0 to 256, int8 and int4, and 1470 calls drawn
+// from 2 to 7001 tokens of the projections of d = 768 to 2560 in steps of 128.  On
+// drawn calls that a fit had not seen, the choice between these forms and the
+// many-token tiles takes 0.3% more time than the fastest form up to 64 tokens, 0.8%
+// up to 512 and 1.2% above; fitted on the grid alone, with neither E nor m, 2.2%, and
+// 24% just short of a full round (957 x 1920 x 7996 44.0 us, the fastest 35.5).
 struct MidForm {
   int tt, rt;
-  double c[8], big[8];
+  int res[2];  // R up to rank 64, and above
+  double c[2][13];
 };
 constexpr MidForm kMidForms[] = {
     // 64 x 64, 8 waves; 4 waves
-    {4, 4,
-     {6.494, 1.192, 2.777, 1.211, 1.761, 0.306, 0.072, 1.777},
-     {6.254, 1.282, 9.309, -0.792, -4.856, 2.348, 1.218, 2.058}},
-    {4, 4,
-     {8.319, 1.331, 1.041, 0.290, 1.818, 1.043, -0.681, -0.522},
-     {7.243, 1.379, 0.748, 0.093, 2.359, 0.972, 1.376, 0.937}},
+    {4, 4, {1, 1},
+     {{6.356, 1.044, 3.700, 1.010, 0.362, 0.744, 0, 0, 1.224, 0.217, -0.070, 0.543, -0.013},
+      {5.715, 1.292, 2.079, 0.329, 2.390, 1.497, 0, 0, 2.642, -0.215, 1.230, 1.687, -0.219}}},
+    {4, 4, {2, 2},
+     {{8.408, 1.257, 0.050, 1.116, 1.334, 0.187, 2.776, 0.045, 0.821, 0.069, -1.180, -0.570, 0.025},
+      {6.571, 1.657, 1.404, -0.073, -0.876, 1.586, 4.783, -0.514, 1.148, -0.448, 1.411, 0.854, -0.008}}},
     // 32 x 64, 8 waves; 4 waves
-    {2, 4,
-     {5.564, 0.721, 2.408, 0.482, 0.218, 0.507, 0.282, 1.350},
-     {5.754, 0.712, 1.226, 0.571, 4.151, -0.002, 1.169, 0.551}},
-    {2, 4,
-     {5.904, 0.994, 0.387, 0.238, 1.014, 0.456, -0.086, -0.312},
-     {5.497, 0.970, 0.564, -0.052, 1.626, 0.752, 1.246, 0.571}},
+    {2, 4, {1, 1},
+     {{5.514, 0.729, 3.125, 0.424, 0.341, 0.441, 0, 0, 0.425, 0.038, 0.222, 0.177, 0.079},
+      {5.626, 0.642, 0.616, 0.439, 4.061, 0.183, 0, 0, 0.556, 0.152, 1.426, 0.679, 0.156}}},
+    {2, 4, {3, 2},
+     {{6.020, 1.011, 0.080, 0.278, 0.746, 0.555, 1.479, -0.158, 0.291, -0.038, -0.448, -0.101, -0.046},
+      {5.713, 0.917, 0.408, 0.017, 2.105, 0.183, -0.401, 0.948, -0.474, 0.138, 1.258, 0.511, -0.041}}},
     // 16 x 64, 4 waves; 16 x 32 and 16 x 16, 8 waves
-    {1, 4,
-     {4.788, 0.821, 0.286, 0.071, 0.559, 0.379, 0.718, -0.129},
-     {5.320, 0.744, 0.927, -0.002, 0.586, 0.292, 1.208, 0.260}},
-    {1, 2,
-     {4.691, 0.440, 0.452, 0.095, 0.733, 0.140, 0.543, 0.457},
-     {4.927, 0.447, 0.956, 0.394, 0.134, -0.003, 1.092, 0.272}},
-    {1, 1,
-     {4.207, 0.451, 0.571, 0.075, 0.656, 0.128, 0.622, -0.092},
-     {4.623, 0.429, 0.646, 0.154, 1.102, 0.115, 1.027, 0.020}},
+    {1, 4, {4, 3},
+     {{4.983, 0.827, 0.318, 0.235, 0.399, 0.192, 0.643, 0.164, -0.248, -0.014, 0.478, -0.049, -0.019},
+      {5.309, 0.757, 0.039, 0.103, 1.764, 0.133, -0.438, 0.246, -0.066, -0.042, 1.186, 0.171, 0.229}}},
+    {1, 2, {2, 1},
+     {{4.781, 0.430, 0.516, 0.001, -0.078, 0.129, 1.933, 0.120, 0.022, 0.087, 0.370, 0.539, 0.060},
+      {5.141, 0.418, 0.821, 0.416, 0.069, -0.050, 0, 0, -0.366, 0.091, 1.066, 0.367, 0.164}}},
+    {1, 1, {2, 1},
+     {{4.308, 0.422, 0.561, -0.090, -0.563, 0.264, 2.404, 0.047, 0.013, 0.161, 0.351, 0.440, 0.159},
+      {4.665, 0.418, 0.514, 0.121, 1.435, 0.137, 0, 0, 0.024, 0.045, 1.009, -0.111, 0.109}}},
 };
 struct MidPlan {
   int form;
@@ -589,10 +595,12 @@ MidPlan plan_mid(int64_t M, int64_t K, int64_t N, int64_t r) {
     const int64_t tb = dfssm::ceil_div(M, 16 * F.tt);
     const double blocks = (double)tb * (double)(dfssm::ceil_div(N, 16 * F.rt) + std::max<int64_t>(1, dfssm::ceil_div(r, 16)));
     const double x = blocks / cus, e = std::max(0.0, std::ceil(x) - 1.0), s = std::max(0.0, x - 1.0);
-    const double* c = r <= 64 ? F.c : F.big;
-    const double rank = r <= 64 ? (c[6] + c[7] * std::min(1.0, e)) * (double)dfssm::ceil_div(r, 16) / 4.0
-                                : (c[6] + c[7] * s) * (double)(dfssm::ceil_div(r, 64) - 1);
-    const double us = c[0] + c[1] * k + (c[2] + c[3] * k) * e + (c[4] + c[5] * k) * s + rank;
+    const double E = std::max(0.0, std::ceil(x / F.res[r > 64]) - 1.0), m = std::min(1.0, x);
+    const double* c = F.c[r > 64];
+    const double rank = r <= 64 ? (c[10] + c[11] * std::min(1.0, e)) * (double)dfssm::ceil_div(r, 16) / 4.0
+                                : (c[10] + c[11] * s) * (double)(dfssm::ceil_div(r, 64) - 1);
+    const double us = c[0] + c[1] * k + (c[2] + c[3] * k) * e + (c[4] + c[5] * k) * s + (c[6] + c[7] * k) * E +
+                      (c[8] + c[9] * k) * m + (N % 16 ? c[12] * x : 0.0) + rank;
     if (us < best.us) best = {f, us};
   }
   return best;

@@ -610,21 +610,21 @@ hipError_t launch_tile(TileArgs a, hipStream_t st) {
 
 // The two tile forms: 128 tokens x 256 rows (runs of up to 17 row tiles; a wave
 // holds 128 x 64, each expanded sign operand feeds 8 MFMAs) and 128 x 128
-// (a wave 64 x 64: twice the workgroups).  Modelled cost (us, both
-// launches) with x = workgroups per CU and k = K / 1024:
-//   c0 + c1 k + (c2 + c3 k) (ceil(x) - 1) + (c4 + c5 k) (x - 1) + c6 k M / 1000
-// (x > 1); above rank 64, which takes the 128 x 128 form, with g = further chunks
-// of 64 ranks, coefficients of its own and g (c7 + c8 M / 1000) more.  Fitted on
-// MI355X to 24 to 4096 tokens on 16 shapes (K = 512 to 8192, N = 512 to 10576),
-// r = 0 to 256, as the split-K tile kernel's cost is.
+// (a wave 64 x 64: twice the workgroups).  Modelled cost (us, both launches) with x =
+// workgroups per CU, of which two fit at once, E = ceil(x / 2) - 1 and k = K / 1024:
+//   c0 + c1 k + (c2 + c3 k) x + (c4 + c5 k) E, and c6 x where N % 16 != 0
+// (a token's outputs then start off the 64-byte segments of a tile's stores: at x = 1,
+// K = 2048 about 4 us of the wide form's 40); above rank 64, which takes the 128 x 128
+// form, with g = further chunks of 64 ranks, coefficients of its own and
+// g (c7 + c8 M / 1000) more.  Fitted on MI355X as the split-K tile kernel's cost is.
 struct TilePlan {
   bool wide;
   double us;
 };
 TilePlan plan_tile(int64_t M, int64_t K, int64_t N, int64_t r) {
-  static constexpr double kC[3][9] = {{12.674, 5.758, 4.943, 0.463, 0.518, 2.364, -0.012, 0, 0},
-                                      {19.094, 7.159, 2.719, 2.327, 5.523, 1.937, 0.128, 0, 0},
-                                      {11.609, 6.155, 7.330, 0.378, 1.778, 2.368, 0.073, 2.658, 1.026}};
+  static constexpr double kC[3][9] = {{13.633, 3.661, 2.705, 2.233, 1.945, 2.595, 0.967, 0, 0},
+                                      {20.355, 4.992, 2.736, 3.346, 4.576, 4.202, 3.817, 0, 0},
+                                      {8.805, 5.473, 4.868, 1.292, 2.944, 4.354, 2.101, 2.709, 1.672}};
   const int cus = dfssm::device_cu_count();
   const int64_t tb = dfssm::ceil_div(M, 128);
   const double k = (double)K / 1024.0, m = (double)M / 1000.0;
@@ -632,9 +632,9 @@ TilePlan plan_tile(int64_t M, int64_t K, int64_t N, int64_t r) {
   TilePlan p{false, 0.0};
   for (int f = 0; f < (r > 64 ? 1 : 2); ++f) {
     const int64_t rb = f ? wide_runs(tb, dfssm::ceil_div(N, 16)) : dfssm::ceil_div(N, 128);
-    const double x = (double)(tb * rb) / cus, e = std::max(0.0, std::ceil(x) - 1.0), s = std::max(0.0, x - 1.0);
+    const double x = (double)(tb * rb) / cus, E = std::max(0.0, std::ceil(x / 2) - 1.0);
     const double* c = kC[r > 64 ? 2 : f];
-    const double us = c[0] + c[1] * k + (c[2] + c[3] * k) * e + (c[4] + c[5] * k) * s + c[6] * k * m + g * (c[7] + c[8] * m);
+    const double us = c[0] + c[1] * k + (c[2] + c[3] * k) * x + (c[4] + c[5] * k) * E + (N % 16 ? c[6] * x : 0.0) + g * (c[7] + c[8] * m);
     if (f == 0 || us < p.us) p = {f == 1, us};
   }
   // test switch prefill_kernel: 4 the 128 x 128 form, 8 the wide one
