@@ -536,48 +536,49 @@ hipError_t launch_t(MidArgs a, hipStream_t st) {
 // x - 1), E = ceil(x / R) - 1, m = min(1, x) and k = K / 1024,
 //   c0 + c1 k + (c2 + c3 k) e + (c4 + c5 k) s + (c6 + c7 k) E + (c8 + c9 k) m,
 // that is one workgroup's chain of latencies, what further workgroups on a CU add,
-// what they share, a step for every further round and how full the first is; c12 x
+// what they share, a step for every further round and how full the first is; c10 x
 // where N % 16 != 0 (a token's outputs then start off the 64-byte segments of a
-// tile's stores); and (c10 + c11 min(1, e)) ceil(r / 16) / 4 up to rank 64, or above,
-// with coefficients of their own, (c10 + c11 s) g for g further chunks of 64 ranks.
-// Fitted on MI355X, each call of a graph on weights of its own (400 MB of them in
-// turn, as a decode step meets them): a grid of 3 to 4096 tokens on 19 shapes (K =
-// 512 to 16384 x N = 512 to 9600), r = 0 to 256, int8 and int4, and 1470 calls drawn
-// from 2 to 7001 tokens of the projections of d = 768 to 2560 in steps of 128.  On
-// drawn calls that a fit had not seen, the choice between these forms and the
+// tile's stores); c11 x l with l = M K / 4 MB - 1 within 0 .. 1 (the codes outgrow an
+// XCD's L2); and (c12 + c13 min(1, e)) ceil(r / 16) / 4 up to rank 64, or above, with
+// coefficients of their own, (c12 + c13 s) g for g further chunks of 64 ranks.  Fitted
+// on MI355X, slopes held above 0, each call of a graph on weights of its own (400 MB
+// of them in turn, as a decode step meets them): a grid of 3 to 4096 tokens on 19
+// shapes (K = 512 to 16384 x N = 512 to 9600), r = 0 to 256, int8 and int4, and 1470
+// calls drawn from 2 to 7001 tokens of the projections of d = 768 to 2560 in steps of
+// 128.  On drawn calls that a fit had not seen, the choice between these forms and the
 // many-token tiles takes 0.3% more time than the fastest form up to 64 tokens, 0.8%
-// up to 512 and 1.2% above; fitted on the grid alone, with neither E nor m, 2.2%, and
-// 24% just short of a full round (957 x 1920 x 7996 44.0 us, the fastest 35.5).
+// above; fitted on the grid alone, with neither E, m nor l, 2.2%, and 24% just short
+// of a full round (957 x 1920 x 7996 44.0 us, the fastest 35.5).
 struct MidForm {
   int tt, rt;
   int res[2];  // R up to rank 64, and above
-  double c[2][13];
+  double c[2][14];
 };
 constexpr MidForm kMidForms[] = {
     // 64 x 64, 8 waves; 4 waves
     {4, 4, {1, 1},
-     {{6.356, 1.044, 3.700, 1.010, 0.362, 0.744, 0, 0, 1.224, 0.217, -0.070, 0.543, -0.013},
-      {5.715, 1.292, 2.079, 0.329, 2.390, 1.497, 0, 0, 2.642, -0.215, 1.230, 1.687, -0.219}}},
+     {{6.611, 1.031, 1.908, 1.042, 2.681, 0.504, 0, 0, 0.844, 0.243, -0.012, 1.142, -0.040, 0.980},
+      {5.910, 1.099, 1.169, 0.486, 5.172, 1.082, 0, 0, 2.023, 0.071, 0.084, 0.651, 1.345, 1.152}}},
     {4, 4, {2, 2},
-     {{8.408, 1.257, 0.050, 1.116, 1.334, 0.187, 2.776, 0.045, 0.821, 0.069, -1.180, -0.570, 0.025},
-      {6.571, 1.657, 1.404, -0.073, -0.876, 1.586, 4.783, -0.514, 1.148, -0.448, 1.411, 0.854, -0.008}}},
+     {{8.533, 1.326, 0, 0.968, 1.903, 0.060, 2.538, 0, 0.658, 0.050, 0.018, 1.946, -1.389, -0.279},
+      {6.751, 1.410, 0.724, 0.010, 0.638, 1.187, 3.523, 0, 1.032, -0.158, -0.126, 1.048, 1.472, 0.791}}},
     // 32 x 64, 8 waves; 4 waves
     {2, 4, {1, 1},
-     {{5.514, 0.729, 3.125, 0.424, 0.341, 0.441, 0, 0, 0.425, 0.038, 0.222, 0.177, 0.079},
-      {5.626, 0.642, 0.616, 0.439, 4.061, 0.183, 0, 0, 0.556, 0.152, 1.426, 0.679, 0.156}}},
+     {{5.288, 0.749, 2.034, 0.497, 1.359, 0.385, 0, 0, 0.737, -0.004, 0.059, 0.298, 0.272, 0.291},
+      {5.127, 0.733, 0.619, 0.432, 3.698, 0.303, 0, 0, 1.252, 0.081, 0.248, 0, 1.251, 0.585}}},
     {2, 4, {3, 2},
-     {{6.020, 1.011, 0.080, 0.278, 0.746, 0.555, 1.479, -0.158, 0.291, -0.038, -0.448, -0.101, -0.046},
-      {5.713, 0.917, 0.408, 0.017, 2.105, 0.183, -0.401, 0.948, -0.474, 0.138, 1.258, 0.511, -0.041}}},
+     {{6.038, 0.988, 0, 0.325, 1.028, 0.379, 0.964, 0, 0.196, 0.016, 0.007, 0.568, -0.491, 0.003},
+      {5.323, 0.998, 0.284, 0.018, 1.972, 0.358, 0.550, 0.515, 0.159, 0.004, -0.001, 1.872, 1.253, 0.339}}},
     // 16 x 64, 4 waves; 16 x 32 and 16 x 16, 8 waves
     {1, 4, {4, 3},
-     {{4.983, 0.827, 0.318, 0.235, 0.399, 0.192, 0.643, 0.164, -0.248, -0.014, 0.478, -0.049, -0.019},
-      {5.309, 0.757, 0.039, 0.103, 1.764, 0.133, -0.438, 0.246, -0.066, -0.042, 1.186, 0.171, 0.229}}},
+     {{4.829, 0.829, 0.236, 0.236, 0.463, 0.191, 0.764, 0.105, -0.043, -0.015, -0.015, 0.077, 0.494, -0.072},
+      {5.335, 0.736, 0.214, 0.090, 1.382, 0.184, 0, 0.097, -0.034, -0.033, 0.146, 0.457, 1.188, 0.164}}},
     {1, 2, {2, 1},
-     {{4.781, 0.430, 0.516, 0.001, -0.078, 0.129, 1.933, 0.120, 0.022, 0.087, 0.370, 0.539, 0.060},
-      {5.141, 0.418, 0.821, 0.416, 0.069, -0.050, 0, 0, -0.366, 0.091, 1.066, 0.367, 0.164}}},
+     {{4.754, 0.431, 0.492, 0, 0.032, 0.124, 1.649, 0.133, -0.012, 0.082, 0.089, 0.656, 0.424, 0.498},
+      {5.126, 0.420, 0.886, 0.389, 0.110, 0, 0, 0, -0.393, 0.096, 0.204, 0.284, 1.072, 0.174}}},
     {1, 1, {2, 1},
-     {{4.308, 0.422, 0.561, -0.090, -0.563, 0.264, 2.404, 0.047, 0.013, 0.161, 0.351, 0.440, 0.159},
-      {4.665, 0.418, 0.514, 0.121, 1.435, 0.137, 0, 0, 0.024, 0.045, 1.009, -0.111, 0.109}}},
+     {{4.242, 0.436, 0.421, 0, 0.035, 0.126, 1.803, 0, 0.092, 0.109, 0.112, 1.384, 0.441, 0.215},
+      {4.634, 0.427, 0.390, 0.156, 0.603, 0.146, 0, 0, 0.086, 0.026, 0.083, 0, 1.006, 0.153}}},
 };
 struct MidPlan {
   int form;
@@ -590,6 +591,7 @@ MidPlan plan_mid(int64_t M, int64_t K, int64_t N, int64_t r) {
   MidPlan best{0, std::numeric_limits<double>::infinity()};
   const int cus = dfssm::device_cu_count();
   const double k = (double)K / 1024.0;
+  const double l = std::min(1.0, std::max(0.0, (double)M * (double)K / 4194304.0 - 1.0));
   for (int f = 0; f < (int)(sizeof(kMidForms) / sizeof(kMidForms[0])); ++f) {
     const MidForm& F = kMidForms[f];
     const int64_t tb = dfssm::ceil_div(M, 16 * F.tt);
@@ -597,10 +599,10 @@ MidPlan plan_mid(int64_t M, int64_t K, int64_t N, int64_t r) {
     const double x = blocks / cus, e = std::max(0.0, std::ceil(x) - 1.0), s = std::max(0.0, x - 1.0);
     const double E = std::max(0.0, std::ceil(x / F.res[r > 64]) - 1.0), m = std::min(1.0, x);
     const double* c = F.c[r > 64];
-    const double rank = r <= 64 ? (c[10] + c[11] * std::min(1.0, e)) * (double)dfssm::ceil_div(r, 16) / 4.0
-                                : (c[10] + c[11] * s) * (double)(dfssm::ceil_div(r, 64) - 1);
+    const double rank = r <= 64 ? (c[12] + c[13] * std::min(1.0, e)) * (double)dfssm::ceil_div(r, 16) / 4.0
+                                : (c[12] + c[13] * s) * (double)(dfssm::ceil_div(r, 64) - 1);
     const double us = c[0] + c[1] * k + (c[2] + c[3] * k) * e + (c[4] + c[5] * k) * s + (c[6] + c[7] * k) * E +
-                      (c[8] + c[9] * k) * m + (N % 16 ? c[12] * x : 0.0) + rank;
+                      (c[8] + c[9] * k) * m + (N % 16 ? c[10] * x : 0.0) + c[11] * x * l + rank;
     if (us < best.us) best = {f, us};
   }
   return best;

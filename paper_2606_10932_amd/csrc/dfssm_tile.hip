@@ -622,9 +622,9 @@ struct TilePlan {
   double us;
 };
 TilePlan plan_tile(int64_t M, int64_t K, int64_t N, int64_t r) {
-  static constexpr double kC[3][9] = {{13.633, 3.661, 2.705, 2.233, 1.945, 2.595, 0.967, 0, 0},
-                                      {20.355, 4.992, 2.736, 3.346, 4.576, 4.202, 3.817, 0, 0},
-                                      {8.805, 5.473, 4.868, 1.292, 2.944, 4.354, 2.101, 2.709, 1.672}};
+  static constexpr double kC[3][9] = {{12.535, 4.082, 3.424, 1.935, 0.853, 3.064, 0.948, 0, 0},
+                                      {21.663, 4.499, 1.612, 3.777, 6.643, 3.516, 3.689, 0, 0},
+                                      {8.939, 5.429, 4.744, 1.360, 3.143, 4.294, 2.012, 2.764, 1.617}};
   const int cus = dfssm::device_cu_count();
   const int64_t tb = dfssm::ceil_div(M, 128);
   const double k = (double)K / 1024.0, m = (double)M / 1000.0;
